@@ -21,7 +21,7 @@
  * Error behaviour: every entry point returns ELAS_OK (0) or a negative
  * ELAS_ERR_* code; no C++ exception crosses this interface. After a failure
  * elas_last_error() describes it. Work that fails on the device after a
- * call has returned (the device mesh exhausting its flip rounds or failing a
+ * call has returned (the device mesh reaching its walk limit or failing a
  * consistency check; its frame is then matched without plane priors, so its
  * maps differ from the reference pipeline) is reported as ELAS_ERR_INTERNAL:
  * the failing kernel sets a pinned report word of the calling handle, and the
@@ -127,9 +127,9 @@ typedef struct elas_stats {
   int32_t n_tri_left;          /* triangles of the left-view mesh */
   int32_t n_tri_right;
   double  host_mesh_ms;        /* host time spent triangulating (both views) */
-  int32_t mesh_rounds[2];      /* device mesh: synchronous flip rounds, left and right
-                                  view (0 when meshed on the host) */
-  int32_t mesh_flips[2];       /* device mesh: edge flips, left and right view */
+  int32_t mesh_rounds[2];      /* device mesh: most triangles owned by one support point,
+                                  left and right view (0 when meshed on the host) */
+  int32_t mesh_flips[2];       /* 0: the device mesh is built without edge flips */
 } elas_stats;
 
 /* Per-kernel device times of the most recent elas_process call (only while
@@ -376,10 +376,11 @@ ELAS_API int elas_server_destroy(elas_server* s);
  * if a device mesh failed since the last call. */
 ELAS_API int elas_get_stats(elas_handle* h, elas_stats* out);
 
-/* Test hook: caps the flip rounds of the device mesh that builds Section
- * III-A's Delaunay triangulation (1..32000, larger values clamp; the default
- * 32000 never binds, a frame needs a few tens; ELAS_ERR_ARG below 1). A view that is not legal
- * within the cap gives up, its frame is matched without plane priors, and the
+/* Test hook: caps the rounds of the device mesh that builds Section III-A's
+ * Delaunay triangulation, the neighbours a support point visits in either
+ * direction (1..32000, larger values clamp; the default 32000 never binds, a
+ * point needs about ten; ELAS_ERR_ARG below 1). A view with a point that needs
+ * more gives up, its frame is matched without plane priors, and the
  * failure is reported as described at the top of this header. Lets tests
  * force the failure path while every kernel still exits normally. */
 ELAS_API int elas_set_mesh_round_limit(elas_handle* h, int32_t rounds);

@@ -37,8 +37,8 @@ thread_local std::string g_create_error;
 // Timed kernels of elas_process, each with a start/stop event pair taken by
 // hipExtLaunchKernel from the kernel's own dispatch: descriptor, support,
 // filter, past-only redundancy, rows, mesh (host mode: events around the host
-// step and its upload), raster, dense, check, median.
-constexpr int kTimed = 10;
+// step and its upload), raster, dense, check, median, the mesh's triangles.
+constexpr int kTimed = 11;
 
 // One background host thread that builds the right view's mesh while the
 // calling thread builds the left one (host mesh mode).
@@ -257,7 +257,7 @@ int take_mesh_failure(elas_handle* h) {
   return fail(h, ELAS_ERR_INTERNAL,
               std::string("the device mesh of an earlier frame on this handle failed (status ") +
                   std::to_string(st) +
-                  (st == 1 ? ", flip rounds exhausted" : ", consistency check") +
+                  (st == 1 ? ", walk limit reached" : ", consistency check") +
                   "); that frame's maps were computed without plane priors");
 }
 
@@ -958,7 +958,7 @@ int elas::process_one(elas_handle* h, const uint8_t* left, const uint8_t* right,
   // one stage; while timing, kernel k records its start/stop events
   auto run = [&](int k, int32_t stage, int variant) -> hipError_t {
     if (!timed) return launch_stage(stage, F, variant, stream);
-    if (stage == kStageMesh || stage_blocks(stage, F.g, F.p, variant) > 0) h->kev_used[k] = true;
+    if (stage_blocks(stage, F.g, F.p, variant) > 0) h->kev_used[k] = true;
     return launch_stage(stage, F, variant, stream, h->kev[k][0], h->kev[k][1]);
   };
   HIP_TRY(run(0, kStageDescriptor, var.first));
@@ -976,6 +976,7 @@ int elas::process_one(elas_handle* h, const uint8_t* left, const uint8_t* right,
     }
   } else {
     HIP_TRY(run(5, kStageMesh, 0));
+    HIP_TRY(run(10, kStageTris, 0));
   }
   HIP_TRY(run(6, kStageRaster, 0));
   HIP_TRY(run(7, kStageDense, var.second));
@@ -1380,7 +1381,7 @@ int elas::process_batch(elas_handle* h, int32_t n, const elas_pair* pairs, hipSt
     // events; stages without workgroups launch nothing and are left out
     std::vector<LaunchRec> run;
     for (const LaunchRec& r : recs)
-      if (r.total > 0 || r.stage == kStageMesh) run.push_back(r);
+      if (r.total > 0) run.push_back(r);
     while (h->bev.size() < 2 * run.size()) {
       hipEvent_t e = nullptr;
       HIP_TRY(hipEventCreate(&e));
@@ -1566,7 +1567,7 @@ int elas_get_timing(elas_handle* h, elas_timing* out) {
     out->support_ms = st[kStageSupport];
     out->filter_ms = st[kStageFilter] + st[kStageRedun];
     out->rows_ms = st[kStageRows];
-    out->mesh_ms = st[kStageMesh];
+    out->mesh_ms = st[kStageMesh] + st[kStageTris];
     out->raster_ms = st[kStageRaster];
     out->dense_ms = st[kStageDense];
     out->lrcheck_ms = st[kStageCheck] + st[kStageMedian];
@@ -1575,8 +1576,8 @@ int elas_get_timing(elas_handle* h, elas_timing* out) {
   }
   if (!h->have_result || !h->have_timing)
     return fail(h, ELAS_ERR_ARG, "no completed call with timing enabled");
-  int last = 0;
-  for (int k = 0; k < kTimed; ++k)
+  int last = 0;  // the last launch of the chain: check or median
+  for (int k = 0; k < 10; ++k)
     if (h->kev_used[k]) last = k;
   HIP_TRY(hipEventSynchronize(h->kev[last][1]));
   float ms[kTimed] = {};
@@ -1588,7 +1589,7 @@ int elas_get_timing(elas_handle* h, elas_timing* out) {
   out->support_ms = ms[1];
   out->filter_ms = ms[2] + ms[3];
   out->rows_ms = ms[4];
-  out->mesh_ms = ms[5];
+  out->mesh_ms = ms[5] + ms[10];
   out->raster_ms = ms[6];
   out->dense_ms = ms[7];
   out->lrcheck_ms = ms[8] + ms[9];

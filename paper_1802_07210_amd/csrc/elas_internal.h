@@ -10,13 +10,13 @@ namespace elas {
 
 constexpr int kMaxD = 256;
 constexpr int32_t kNoOwner = 0x7FFFFFFF;
-constexpr int kMeshLdsBytes = 160 * 1024 - 2048;  // dynamic LDS of one mesh workgroup
 // Frames meshed on the device have both sides at most this long: the mesh
-// packs a point into a 32-bit key with 12-bit coordinates, and its fp64
-// in-circle test is exact only for coordinates below 2^12.
+// packs a point into a 32-bit key with 12-bit coordinates, and its circle
+// comparisons are exact only for coordinates below 2^12.
 constexpr int kDeviceMeshMaxSide = 4096;
-// Flip rounds a device mesh view may take before it reports failure; far
-// above what any frame needs (17 at 640x480), so it only binds when lowered.
+// Neighbours a device mesh point may visit in one direction before its view
+// reports failure; far above what any frame needs (tens), so it only binds
+// when lowered.
 constexpr int kMeshMaxRounds = 32000;
 
 // Image, lattice and grid geometry of one (w, h) for one parameter set.
@@ -54,7 +54,7 @@ struct KParams {
   int32_t redundancy;   // 0: two-sided; 1: past-only
   int32_t subsample;    // keep every k-th support point
   int32_t median;       // 0: no median; 3 or 5: median window
-  int32_t mesh_max_rounds;  // flip rounds before the device mesh gives up (a test
+  int32_t mesh_max_rounds;  // walk steps before the device mesh gives up (a test
                             // hook lowers it; the default never binds)
 };
 
@@ -74,10 +74,11 @@ struct MeshHeader {
   int32_t ntri[2];       // triangles (2n + 2, or 0 without support points)
   int32_t corners[8];    // d of the four image corners, left then right view
   int64_t support_evals; // support-search evaluations of the frame
-  int32_t status[2];     // 0; 1 if a view's flip rounds hit their limit; 2 if its
-                         // initial triangulation failed a consistency check
-  int32_t rounds[2];     // device mesh: flip rounds of each view (0 on the host)
-  int32_t flips[2];      // device mesh: edge flips of each view
+  int32_t status[2];     // 0; 1 if a walk hit its limit; 2 if the view's triangle
+                         // count failed its consistency check
+  int32_t rounds[2];     // device mesh: most triangles owned by one point of each
+                         // view (0 on the host)
+  int32_t flips[2];      // 0 (the mesh is built without flips)
 };
 
 // ---- host mesh builder (elas_mesh.cpp) ----------------------------------
@@ -179,6 +180,16 @@ __device__ __forceinline__ Frame global_frame(const Frame& t, const char* base) 
   return F;
 }
 
+// Frame of logical block b in a batch: the last frame starting at or before b.
+__device__ __forceinline__ int frame_of(const int32_t* __restrict__ starts, int nf, int b) {
+  int lo = 0, hi = nf - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (starts[mid] <= b) lo = mid; else hi = mid - 1;
+  }
+  return lo;
+}
+
 // Stages of the path, in launch order.
 // kStageRedun (past-only redundancy) and kStageMedian have no blocks unless
 // the parameters select them.
@@ -188,7 +199,8 @@ enum Stage : int32_t {
   kStageFilter,
   kStageRedun,
   kStageRows,
-  kStageMesh,
+  kStageMesh,   // the mesh's walks
+  kStageTris,   // its triangles in canonical order
   kStageRaster,
   kStageDense,
   kStageCheck,
@@ -229,13 +241,18 @@ hipError_t launch_stage_batch(int32_t stage, const Frame* frames, const int32_t*
 // same number, else 0.
 int32_t uniform_blocks(const int32_t* starts, int32_t nf);
 
-// The mesh stage (elas_mesh_device.hip): two workgroups per frame, for
-// frames with both sides at most kDeviceMeshMaxSide.
-hipError_t launch_mesh_frame(const Frame& f, hipStream_t s, hipEvent_t start = nullptr,
-                             hipEvent_t stop = nullptr);
-hipError_t launch_mesh_batch(const Frame* frames, int32_t nf, hipStream_t s,
-                             hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
-// Device mesh scratch per view (views that do not fit in LDS).
+// The two mesh stages, kStageMesh and kStageTris (elas_mesh_device.hip), for
+// frames with both sides at most kDeviceMeshMaxSide: workgroups of one frame,
+// dynamic LDS of kStageMesh, and the launches.
+int32_t mesh_blocks(int32_t stage, const Geometry& g, bool batch);
+size_t mesh_lds(const Geometry& g);
+hipError_t launch_mesh_frame(int32_t stage, const Frame& f, hipStream_t s, hipEvent_t start,
+                             hipEvent_t stop);
+hipError_t launch_mesh_batch(int32_t stage, const Frame* frames, const int32_t* starts, int32_t nf,
+                             int32_t total, int32_t bpf, uint32_t bmul, size_t lds, hipStream_t s,
+                             hipEvent_t start, hipEvent_t stop);
+// Device mesh scratch per view. Its first word counts the triangles in the
+// overflow list and is cleared by the rows stage.
 size_t mesh_global_scratch_per_view(const Geometry& g);
 // Blocks of the dense launch for a tile variant (one candidate-count entry
 // per block); the count array is sized for the largest, dense_blocks_max.

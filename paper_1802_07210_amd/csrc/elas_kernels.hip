@@ -54,16 +54,6 @@ __device__ __forceinline__ int xcd_remap(int b, int n) {
   return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + i;
 }
 
-// Frame of logical block b in a batch: the last frame starting at or before b.
-__device__ __forceinline__ int frame_of(const int32_t* __restrict__ starts, int nf, int b) {
-  int lo = 0, hi = nf - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (starts[mid] <= b) lo = mid; else hi = mid - 1;
-  }
-  return lo;
-}
-
 inline int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
 __host__ __device__ __forceinline__ int cdivd(int a, int b) { return (a + b - 1) / b; }
 
@@ -1050,6 +1040,11 @@ __device__ __forceinline__ void rows_body(const Frame& F, int lb) {
   int32_t* hrowR = F.rowsR;
   uint32_t* gridL = F.gridL;
   uint32_t* gridR = F.gridR;
+  // the device mesh's status words and overflow counters start at 0
+  if (lb == 0 && lane < 2 && F.mesh_scratch_per_view) {
+    F.hdr->status[lane] = 0;
+    *reinterpret_cast<int32_t*>(F.mesh_scratch + lane * F.mesh_scratch_per_view) = 0;
+  }
   for (int x = lane; x < g.w; x += 64) slot[x] = -1;
   __syncthreads();
   int nL = 0, nV = 0, ev = 0;
@@ -2076,7 +2071,8 @@ int32_t stage_blocks(int32_t stage, const Geometry& g, const KParams& p, int dv)
     case kStageFilter: return filter_tiles_x(g) * filter_tiles_y(g);
     case kStageRedun: return p.redundancy ? 1 : 0;
     case kStageRows: return g.lh;
-    case kStageMesh: return 2;
+    case kStageMesh:
+    case kStageTris: return mesh_blocks(stage, g, true);
     case kStageRaster: return 2 * cdiv(g.h, raster_band_rows(g.w));
     case kStageDense: return dense_blocks(g, dv);
     case kStageCheck: return 2 * cdiv((long long)g.w * g.h, 256 * kCheckPx);
@@ -2090,7 +2086,7 @@ size_t stage_lds(int32_t stage, const Geometry& g, const KParams& p) {
     case kStageFilter: return filter_lds_bytes(g, p);
     case kStageRows: return sizeof(int32_t) * (size_t)g.w;
     case kStageRaster: return sizeof(int32_t) * (size_t)raster_band_rows(g.w) * g.w;
-    case kStageMesh: return kMeshLdsBytes;
+    case kStageMesh: return mesh_lds(g);
     case kStageSupport: {
       const int q = support_run(g, p);
       return 32 * (size_t)(support_cols_right(q, g.step, p.D) + support_cols_left(q, g.step, p.D));
@@ -2101,7 +2097,8 @@ size_t stage_lds(int32_t stage, const Geometry& g, const KParams& p) {
 
 hipError_t launch_stage(int32_t stage, const Frame& f, int variant, hipStream_t s,
                         hipEvent_t start, hipEvent_t stop) {
-  if (stage == kStageMesh) return launch_mesh_frame(f, s, start, stop);
+  if (stage == kStageMesh || stage == kStageTris)
+    return launch_mesh_frame(stage, f, s, start, stop);
   const int nb = stage_blocks(stage, f.g, f.p, variant);
   if (nb <= 0) return hipSuccess;
   // the wide raster workgroup when every band of the frame gets a CU
@@ -2162,7 +2159,6 @@ hipError_t launch_stage_batch(int32_t stage, const Frame* frames, const int32_t*
                               int32_t nf, int32_t total_blocks, int32_t bpf, size_t lds,
                               int variant, bool desc_nt, hipStream_t s, hipEvent_t start,
                               hipEvent_t stop) {
-  if (stage == kStageMesh) return launch_mesh_batch(frames, nf, s, start, stop);
   if (total_blocks <= 0 || nf <= 0) return hipSuccess;
   // the multiply path needs bpf >= 2 (bmul < 2^32), bpf * nf == total and
   // b * bpf < 2^32 for every block b
@@ -2170,6 +2166,8 @@ hipError_t launch_stage_batch(int32_t stage, const Frame* frames, const int32_t*
       (uint64_t)total_blocks * (uint64_t)bpf >= (1ull << 32))
     bpf = 0;
   const uint32_t bmul = bpf ? (uint32_t)(((1ull << 32) + (uint64_t)bpf - 1) / (uint64_t)bpf) : 0u;
+  if (stage == kStageMesh || stage == kStageTris)
+    return launch_mesh_batch(stage, frames, starts, nf, total_blocks, bpf, bmul, lds, s, start, stop);
   const dim3 grid(total_blocks), block(stage_threads(stage));
   const uint32_t shm = (uint32_t)lds;
   const bool timed = start || stop;

@@ -332,8 +332,9 @@ class Elas:
         return out
 
     def set_mesh_round_limit(self, rounds: int):
-        """Test hook: caps the device mesh's flip rounds (a frame that needs
-        more fails, reported as ELAS_ERR_INTERNAL by the next call)."""
+        """Test hook: caps the device mesh's rounds, the neighbours a support
+        point visits in either direction (a frame that needs more fails,
+        reported as ELAS_ERR_INTERNAL by the next call)."""
         _check(lib().elas_set_mesh_round_limit(self._h, int(rounds)), self._h)
 
     def set_timing(self, enable: bool):
