@@ -17,6 +17,7 @@
 // for a batch of frames in a single launch (frames in a device table; a
 // block finds its frame in the prefix of the per-frame block counts).
 #include <algorithm>
+#include <type_traits>
 
 #include <hip/hip_ext.h>
 
@@ -941,16 +942,54 @@ __device__ __forceinline__ void filter_body(const Frame& F, int lb) {
 // the top, then along each row from the left, a point is removed iff one of
 // the previous redun_max_dist positions holds a point that survived the same
 // pass with |d' - d| <= redun_threshold. Each line is a sequential chain, so
-// one thread walks one line; the outputs of the last R positions are kept in
-// a register shift ring (R a compile-time bound >= redun_max_dist, so the
-// ring is never indexed at run time). One workgroup per frame: the vertical
-// pass over every column, a barrier, the horizontal pass over every row.
-// Inputs are prefetched eight positions at a time.
+// one thread walks one line, the outputs of the last positions in registers.
+// One workgroup per frame. Bound by that chain: the lattice is staged in LDS
+// (up to kRedunLds bytes of it; larger ones are walked in global memory), so
+// that a step waits for no load, and the default distance has its ring
+// unrolled, which leaves a subtraction, a minimum, a compare and a select from
+// one position to the next (640x480: 46 us from global memory with a shifted
+// ring, 20.5 us now).
 // ---------------------------------------------------------------------------
+constexpr size_t kRedunLds = 150 * 1024;
+
+__host__ __device__ __forceinline__ size_t redun_lds(const Geometry& g) {
+  const size_t bytes = 2 * (size_t)g.lw * (size_t)g.lh;
+  return bytes <= kRedunLds ? (bytes + 15) & ~(size_t)15 : 0;
+}
+
+// Ring of exactly R positions (redun_max_dist = R), R inputs at a time. An
+// empty position (-1) is never within the range [lo, lo + span], lo >= 0.
 template <int R>
-__device__ __forceinline__ void redun_line(const int16_t* __restrict__ in,
-                                           int16_t* __restrict__ out, int n, size_t step,
-                                           int r, int t) {
+__device__ __forceinline__ void redun_line_exact(const int16_t* in, int16_t* out, int n, int step,
+                                                 int t) {
+  int last[R];
+#pragma unroll
+  for (int j = 0; j < R; ++j) last[j] = -1;
+  auto walk = [&](int b0, auto whole) {
+    int x[2 * R];
+#pragma unroll
+    for (int i = 0; i < 2 * R; ++i)
+      x[i] = in[(size_t)(whole.value ? b0 + i : min(b0 + i, n - 1)) * step];
+#pragma unroll
+    for (int i = 0; i < 2 * R; ++i) {
+      const int d = x[i], lo = max(0, d - t);
+      uint32_t near = 0xFFFFFFFFu;  // oldest first: only the last term waits for the step before
+#pragma unroll
+      for (int j = 0; j < R; ++j) near = min(near, (uint32_t)(last[(i + j) % R] - lo));
+      const int res = d >= 0 && near <= (uint32_t)(d + t - lo) ? -1 : d;
+      last[i % R] = res;
+      if (whole.value || b0 + i < n) out[(size_t)(b0 + i) * step] = (int16_t)res;
+    }
+  };
+  int b0 = 0;
+  for (; b0 + 2 * R <= n; b0 += 2 * R) walk(b0, std::true_type{});
+  if (b0 < n) walk(b0, std::false_type{});
+}
+
+// Any distance r <= R: a shifted ring of R positions.
+template <int R>
+__device__ __forceinline__ void redun_line(const int16_t* in, int16_t* out, int n, int step, int r,
+                                           int t) {
   int last[R];
 #pragma unroll
   for (int j = 0; j < R; ++j) last[j] = -1;
@@ -974,29 +1013,46 @@ __device__ __forceinline__ void redun_line(const int16_t* __restrict__ in,
   }
 }
 
-template <int R>
-__device__ __forceinline__ void redun_passes(const Frame& F) {
-  const Geometry g = F.g;
-  const int r = F.p.redun_max_dist, t = F.p.redun_threshold;
-  const int16_t* inc = F.dcan_incon;
-  int16_t* vert = F.dcan_vert;
-  int16_t* fin = F.dcan_final;
-  for (int k = threadIdx.x; k < g.lw; k += blockDim.x)
-    redun_line<R>(inc + k, vert + k, g.lh, (size_t)g.lw, r, t);
-  __syncthreads();
-  for (int l = threadIdx.x; l < g.lh; l += blockDim.x)
-    redun_line<R>(vert + (size_t)l * g.lw, fin + (size_t)l * g.lw, g.lw, 1, r, t);
+__device__ __forceinline__ void redun_any(const int16_t* in, int16_t* out, int n, int step, int r,
+                                          int t) {
+  if (r == 5)
+    redun_line_exact<5>(in, out, n, step, t);
+  else if (r <= 4)
+    redun_line<4>(in, out, n, step, r, t);
+  else if (r <= 8)
+    redun_line<8>(in, out, n, step, r, t);
+  else
+    redun_line<16>(in, out, n, step, r, t);
 }
 
 __device__ __forceinline__ void redun_body(const Frame& F, int lb) {
   (void)lb;
-  const int r = F.p.redun_max_dist;
-  if (r <= 4)
-    redun_passes<4>(F);
-  else if (r <= 8)
-    redun_passes<8>(F);
-  else
-    redun_passes<16>(F);
+  const Geometry g = F.g;
+  const int r = F.p.redun_max_dist, t = min(F.p.redun_threshold, 1 << 12);
+  const int16_t* inc = F.dcan_incon;
+  int16_t* vert = F.dcan_vert;
+  int16_t* fin = F.dcan_final;
+  const int n = g.lw * g.lh, T = (int)blockDim.x, tid = threadIdx.x;
+  if (redun_lds(g) == 0) {
+    for (int k = tid; k < g.lw; k += T) redun_any(inc + k, vert + k, g.lh, g.lw, r, t);
+    __syncthreads();
+    for (int l = tid; l < g.lh; l += T)
+      redun_any(vert + (size_t)l * g.lw, fin + (size_t)l * g.lw, g.lw, 1, r, t);
+    return;
+  }
+  int16_t* const lat = reinterpret_cast<int16_t*>(dyn_smem);
+  stage_copy<8, 1024>((n + 1) / 2,  // the arrays are 256-byte aligned and padded
+                      [&](int i) { return reinterpret_cast<const uint32_t*>(inc)[i]; },
+                      [&](int i, uint32_t x) { reinterpret_cast<uint32_t*>(lat)[i] = x; });
+  __syncthreads();
+  for (int k = tid; k < g.lw; k += T) redun_any(lat + k, lat + k, g.lh, g.lw, r, t);
+  __syncthreads();
+  for (int i = tid; i < n; i += T) vert[i] = lat[i];
+  __syncthreads();
+  for (int l = tid; l < g.lh; l += T)
+    redun_any(lat + (size_t)l * g.lw, lat + (size_t)l * g.lw, g.lw, 1, r, t);
+  __syncthreads();
+  for (int i = tid; i < n; i += T) fin[i] = lat[i];
 }
 
 // ---------------------------------------------------------------------------
@@ -1055,8 +1111,26 @@ __device__ __forceinline__ void rows_body(const Frame& F, int lb) {
   int base = 0;  // survivors in the rows above (global list index of this row's first)
   if (ks > 1) {
     const int n = l * g.lw;
+    // eight entries per load (the array is 256-byte aligned and padded), all
+    // loads of a group in flight together: an entry is empty (-1) iff its
+    // sign bit is set
+    const uint4* fin8 = reinterpret_cast<const uint4*>(fin);
+    const int n8 = n >> 3;
     int c = 0;
-    for (int i = lane; i < n; i += 64) c += fin[i] >= 0 ? 1 : 0;
+    constexpr int kLoads = 8;
+    for (int i0 = 0; i0 < n8; i0 += 64 * kLoads) {
+      uint4 x[kLoads];
+#pragma unroll
+      for (int j = 0; j < kLoads; ++j) x[j] = fin8[min(i0 + 64 * j + lane, n8 - 1)];
+#pragma unroll
+      for (int j = 0; j < kLoads; ++j) {
+        const uint32_t m = 0x80008000u;
+        const int neg = __popc(x[j].x & m) + __popc(x[j].y & m) + __popc(x[j].z & m) +
+                        __popc(x[j].w & m);
+        c += i0 + 64 * j + lane < n8 ? 8 - neg : 0;
+      }
+    }
+    for (int i = 8 * n8 + lane; i < n; i += 64) c += fin[i] >= 0 ? 1 : 0;
     base = wave_sum_i32(c);
   }
   const unsigned long long below = (1ull << lane) - 1ull;
@@ -2085,6 +2159,7 @@ size_t stage_lds(int32_t stage, const Geometry& g, const KParams& p) {
   switch (stage) {
     case kStageFilter: return filter_lds_bytes(g, p);
     case kStageRows: return sizeof(int32_t) * (size_t)g.w;
+    case kStageRedun: return p.redundancy ? redun_lds(g) : 0;
     case kStageRaster: return sizeof(int32_t) * (size_t)raster_band_rows(g.w) * g.w;
     case kStageMesh: return mesh_lds(g);
     case kStageSupport: {
@@ -2200,7 +2275,7 @@ hipError_t launch_stage_batch(int32_t stage, const Frame* frames, const int32_t*
         desc_nt ? go(k_dense_r2nt_batch, 0u) : go(k_dense_r2_batch, 0u);
       break;
     case kStageCheck: go(k_check_batch, 0u); break;
-    case kStageRedun: go(k_redun_batch, 0u); break;
+    case kStageRedun: go(k_redun_batch, shm); break;
     case kStageMedian: go(k_median_batch, 0u); break;
     default: return hipErrorInvalidValue;
   }
