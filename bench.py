@@ -66,8 +66,8 @@ PEAK_SAD_TOPS = 256 * 64 * 2.4e9 * 4 / 1e12    # 157.3 T byte-|diff| per second
 
 STAGES = ["descriptor", "support", "filter", "rows", "mesh", "raster", "dense", "lrcheck"]
 KERNEL_NAMES = {"descriptor": "k_descriptor8", "support": "k_support", "filter": "k_filter",
-                "rows": "k_rows", "mesh": "k_mesh", "raster": "k_raster", "dense": "k_dense_r2",
-                "lrcheck": "k_check"}
+                "rows": "k_rows", "mesh": "k_mesh", "raster": "k_raster", "dense": "k_match",
+                "lrcheck": "k_check"}  # (where rows are too wide for k_match, which checks as well)
 
 
 COPY_BYTES = 256 << 20
@@ -545,7 +545,7 @@ def main():
         # descriptors by non-temporal stores and loads once a batch's reach 192 MiB)
         nt = "nt" if B * 32 * W * H >= (192 << 20) else ""
         names = {s: {"raster": "k_raster256", "descriptor": "k_descriptor16" + nt,
-                     "dense": "k_dense_r2" + nt}.get(s, n) + "_batch"
+                     "dense": "k_match" + nt}.get(s, n) + "_batch"
                  for s, n in names.items()}
     # share of chip time: duration x the fraction of the 256 CUs the kernel's
     # workgroups can occupy (launch geometry of each stage at this size)

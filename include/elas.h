@@ -146,8 +146,12 @@ typedef struct elas_timing {
   float mesh_ms;               /* device mesh kernel, or (mesh_on_host) the host
                                   step and the upload of its records */
   float raster_ms;             /* k_raster */
-  float dense_ms;              /* k_dense, both views */
-  float lrcheck_ms;            /* k_check, plus k_median when a median is set */
+  float dense_ms;              /* k_dense, both views, or the matching part of k_match */
+  float lrcheck_ms;            /* k_check, or the checking part of k_match (rows of up to
+                                  2112 columns; divided by the cycles that its workgroups
+                                  spent in each; in a batch as on the handle's own pairs,
+                                  all in dense_ms where it has none), plus k_median when a
+                                  median is set */
   float device_span_ms;        /* first kernel start to last kernel end, gaps and
                                   host step included */
   double host_wait_ms;         /* calling thread blocked until the lists were ready */

@@ -37,8 +37,8 @@ thread_local std::string g_create_error;
 // Timed kernels of elas_process, each with a start/stop event pair taken by
 // hipExtLaunchKernel from the kernel's own dispatch: descriptor, support,
 // filter, past-only redundancy, rows, mesh (host mode: events around the host
-// step and its upload), raster, dense, check, median, the mesh's triangles.
-constexpr int kTimed = 11;
+// step and its upload), raster, dense, check, median, the mesh's triangles, dense and check in one.
+constexpr int kTimed = 12;
 
 // One background host thread that builds the right view's mesh while the
 // calling thread builds the left one (host mesh mode).
@@ -108,7 +108,7 @@ struct Buffers {
   int32_t *ownerL = nullptr, *ownerR = nullptr;
   int16_t *dplaneL = nullptr, *dplaneR = nullptr, *rawL = nullptr, *rawR = nullptr;
   int32_t* lut = nullptr;
-  int32_t* dense_counts = nullptr;  // candidate evaluations per dense block
+  int32_t* dense_counts = nullptr;  // candidate evaluations per dense block (see Frame)
   // per-row lists (device copy for the device mesh)
   int32_t *rowsL = nullptr, *rowsR = nullptr, *cnt = nullptr;
   // mesh outputs
@@ -981,6 +981,7 @@ int elas::process_one(elas_handle* h, const uint8_t* left, const uint8_t* right,
   HIP_TRY(run(6, kStageRaster, 0));
   HIP_TRY(run(7, kStageDense, var.second));
   HIP_TRY(run(8, kStageCheck, 0));
+  HIP_TRY(run(11, kStageMatch, 0));
   HIP_TRY(run(9, kStageMedian, 0));
   h->have_timing = timed;
   h->have_result = true;
@@ -1145,14 +1146,20 @@ void plan_batch(const std::vector<Frame>& frames, const std::vector<std::pair<in
   };
   const size_t main_table = put(frames.data(), frames.size() * sizeof(Frame));
   for (int32_t st = 0; st < kStageCount; ++st) {
-    const bool tiled = st == kStageDescriptor || st == kStageDense;
-    const int nvar = st == kStageDescriptor ? kDescVariants : (st == kStageDense ? kDenseVariants : 1);
+    const bool tiled = st == kStageDescriptor || st == kStageDense || st == kStageMatch;
+    const int nvar = st == kStageDescriptor
+                         ? kDescVariants
+                         : (st == kStageDense ? kDenseVariants
+                                              : (st == kStageMatch ? kMatchVariants : 1));
     for (int v = 0; v < nvar; ++v) {
       std::vector<Frame> sub;
       std::vector<int32_t> starts(1, 0);
       size_t lds = 0;
       for (size_t i = 0; i < frames.size(); ++i) {
-        const int fv = st == kStageDescriptor ? var[i].first : var[i].second;
+        const int fv = st == kStageDescriptor
+                           ? var[i].first
+                           : (st == kStageDense ? var[i].second
+                                                : match_variant(frames[i].g, frames[i].p));
         if (tiled && fv != v) continue;
         const int dv = tiled ? v : 0;
         sub.push_back(frames[i]);
@@ -1166,7 +1173,8 @@ void plan_batch(const std::vector<Frame>& frames, const std::vector<std::pair<in
       r.nf = (int32_t)sub.size();
       r.total = starts.back();
       r.bpf = uniform_blocks(starts.data(), r.nf);
-      r.desc_nt = (st == kStageDescriptor || st == kStageDense) && desc_nt;
+      r.desc_nt =
+          (st == kStageDescriptor || st == kStageDense || st == kStageMatch) && desc_nt;
       r.lds = lds;
       r.table_off = tiled ? put(sub.data(), sub.size() * sizeof(Frame)) : main_table;
       r.starts_off = put(starts.data(), starts.size() * sizeof(int32_t));
@@ -1214,6 +1222,7 @@ int autotune(elas_handle* h, BatchCtx* c, const std::vector<Frame>& frames,
   const int32_t stages[3] = {kStageDescriptor, kStageDense, kStageSupport};
   std::vector<Frame> fr(frames);
   for (int k = 0; k < 3; ++k) {
+    if (k == 1 && match_fused(fr[0].g, fr[0].p)) continue;  // no dense tiles to choose
     float best_ms = 1e30f;
     const int nvar = k == 0 ? kDescVariants : (k == 1 ? kDenseVariants : 2);
     for (int v = 0; v < nvar; ++v) {
@@ -1534,6 +1543,25 @@ int elas_get_tuned_variants(elas_handle* h, int32_t w, int32_t hp, int32_t* desc
 
 }  // extern "C"
 
+namespace {
+
+// Where one kernel matched and checked: the mean share of its rows' time spent
+// checking, added up over frames (n counts them).
+hipError_t add_check_share(const Buffers* b, const KParams& p, float* sum, int* n) {
+  if (!match_fused(b->g, p)) return hipSuccess;
+  std::vector<int32_t> share(b->g.h);
+  const hipError_t e = hipMemcpy(share.data(), b->dense_counts + b->g.h,
+                                 share.size() * sizeof(int32_t), hipMemcpyDeviceToHost);
+  if (e != hipSuccess) return e;
+  int64_t s = 0;
+  for (int32_t x : share) s += x;
+  *sum += (float)s / (65536.f * (float)b->g.h);
+  *n += 1;
+  return hipSuccess;
+}
+
+}  // namespace
+
 extern "C" {
 
 int elas_set_mesh_round_limit(elas_handle* h, int32_t rounds) {
@@ -1569,16 +1597,24 @@ int elas_get_timing(elas_handle* h, elas_timing* out) {
     out->rows_ms = st[kStageRows];
     out->mesh_ms = st[kStageMesh] + st[kStageTris];
     out->raster_ms = st[kStageRaster];
-    out->dense_ms = st[kStageDense];
-    out->lrcheck_ms = st[kStageCheck] + st[kStageMedian];
+    float share = 0.f;  // of the pairs whose buffers this handle itself holds
+    int n = 0;
+    for (auto& q : h->last_batch) {
+      bool held = false;
+      for (auto& kv : h->pool)
+        for (Buffers* b : kv.second) held |= b == q.b;
+      if (held) HIP_TRY(add_check_share(q.b, h->kp, &share, &n));
+    }
+    const float check = n ? st[kStageMatch] * share / (float)n : 0.f;
+    out->dense_ms = st[kStageDense] + st[kStageMatch] - check;
+    out->lrcheck_ms = st[kStageCheck] + check + st[kStageMedian];
     out->device_span_ms = span;
     return ELAS_OK;
   }
   if (!h->have_result || !h->have_timing)
     return fail(h, ELAS_ERR_ARG, "no completed call with timing enabled");
-  int last = 0;  // the last launch of the chain: check or median
-  for (int k = 0; k < 10; ++k)
-    if (h->kev_used[k]) last = k;
+  // the last launch of the chain: median, check, or dense and check in one
+  const int last = h->kev_used[9] ? 9 : (h->kev_used[11] ? 11 : 8);
   HIP_TRY(hipEventSynchronize(h->kev[last][1]));
   float ms[kTimed] = {};
   for (int k = 0; k < kTimed; ++k)
@@ -1591,8 +1627,11 @@ int elas_get_timing(elas_handle* h, elas_timing* out) {
   out->rows_ms = ms[4];
   out->mesh_ms = ms[5] + ms[10];
   out->raster_ms = ms[6];
-  out->dense_ms = ms[7];
-  out->lrcheck_ms = ms[8] + ms[9];
+  float share = 0.f;
+  int n = 0;
+  if (h->kev_used[11]) HIP_TRY(add_check_share(h->last, h->kp, &share, &n));
+  out->dense_ms = ms[7] + ms[11] * (1.f - share);
+  out->lrcheck_ms = ms[8] + ms[11] * share + ms[9];
   out->device_span_ms = span;
   out->host_wait_ms = h->host_wait_ms;
   out->host_mesh_ms = h->host_mesh_ms;
@@ -1606,7 +1645,9 @@ int elas_get_stats(elas_handle* h, elas_stats* out) {
   int rc = last_header(h, &hd);
   if (rc != ELAS_OK) return rc;
   HIP_TRY(hipStreamSynchronize(h->last_stream));
-  std::vector<int32_t> counts(dense_blocks(h->last->g, h->last_dense_variant));
+  std::vector<int32_t> counts(match_fused(h->last->g, h->kp)
+                                  ? h->last->g.h
+                                  : dense_blocks(h->last->g, h->last_dense_variant));
   HIP_TRY(hipMemcpy(counts.data(), h->last->dense_counts, counts.size() * sizeof(int32_t),
                     hipMemcpyDeviceToHost));
   int64_t cnt = 0;

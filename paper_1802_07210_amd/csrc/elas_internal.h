@@ -144,7 +144,8 @@ struct Frame {
   int16_t* rawL;
   int16_t* rawR;
   const int32_t* lut;
-  int32_t* dense_counts;  // candidate evaluations per dense block
+  int32_t* dense_counts;  // candidate evaluations per dense block; fused: per row, then each
+                          // row's share of time spent checking in 1/65536
   int16_t* outL;
   int16_t* outR;
   int16_t* chkL;         // median mode: checked maps before the median
@@ -204,6 +205,7 @@ enum Stage : int32_t {
   kStageRaster,
   kStageDense,
   kStageCheck,
+  kStageMatch,   // dense matching and check in one, in their place where a row fits
   kStageMedian,
   kStageCount
 };
@@ -211,6 +213,7 @@ enum Stage : int32_t {
 // Tile variants the autotuner chooses between (identical results).
 constexpr int kDescVariants = 3;   // descriptor rows per block: 4, 8, 16
 constexpr int kDenseVariants = 3;  // dense rows per workgroup: 1, 2, 4
+constexpr int kMatchVariants = 2;  // dense matching and check in one, in batches: by row width
 
 // Workgroups one frame needs for a stage (descriptor variant dv).
 int32_t stage_blocks(int32_t stage, const Geometry& g, const KParams& p, int dv);
@@ -258,6 +261,11 @@ size_t mesh_global_scratch_per_view(const Geometry& g);
 // per block); the count array is sized for the largest, dense_blocks_max.
 int32_t dense_blocks(const Geometry& g, int variant);
 int32_t dense_blocks_max(const Geometry& g);
+// Whether a frame's dense matching and check run as kStageMatch (one block, and
+// one candidate-count entry, per row) instead of kStageDense and kStageCheck.
+bool match_fused(const Geometry& g, const KParams& p);
+// The variant (wavefronts per row) of kStageMatch that a frame takes in a batch.
+int match_variant(const Geometry& g, const KParams& p);
 
 }  // namespace elas
 

@@ -1958,6 +1958,187 @@ __device__ __forceinline__ void check_body(const Frame& F, int lb) {
 }
 
 // ---------------------------------------------------------------------------
+// Dense matching of both views and the final check, one image row per
+// workgroup: both views' descriptors of the row are staged in LDS once (every
+// candidate of either view is among them, and so is every own descriptor),
+// the wavefronts take 64-pixel pieces of either view, and the row's two raw
+// maps, in LDS as well, are checked against each other before they leave.
+// Candidates, energies and the check are those of the kernels above. Against
+// them, each descriptor leaves memory once instead of twice, the raw maps are
+// not read back and one launch goes: 32 pairs of 640x480 142 us (from 151 + 22),
+// 8 pairs of 1280x720 110 (108 + 17), one frame of 640x480 10 (10.8 + 4.1). What
+// is left is bound by the integer work of the candidates and by their
+// 16-byte LDS gathers, about even.
+// ---------------------------------------------------------------------------
+template <class DD>
+__host__ __device__ __forceinline__ size_t match_lds_of(int w) {
+  return (2 * (size_t)DD::kBytes + 4) * (size_t)((w + 63) & ~63);
+}
+
+__host__ __device__ __forceinline__ size_t match_lds(const Geometry& g, const KParams& p) {
+  return p.descriptor ? match_lds_of<CensusDense>(g.w) : match_lds_of<GradDense>(g.w);
+}
+// Two rows' workgroups have to fit a CU: rows of up to 2112 columns (census: 3840). There the
+// fused form still gains (4 pairs of 1920x1080: 142 us against 129 + 20; one
+// frame 45 against 35 + 6, which the launch saved makes good). With one row per
+// CU it loses (one frame of 2560x1440: 96 us against 54 + 9, 4 pairs 352 against
+// 199 + 33), so wider rows keep the two kernels.
+constexpr size_t kMatchLds = 76 * 1024;
+// Wavefronts per row: a multiple of four, so that they spread evenly over the
+// SIMDs (5, 6, 7 and 10 were slower than both neighbours), eight for a single
+// frame (its latency is the pieces of one wavefront) and for wide rows of a
+// batch, whose LDS admits few rows per CU; four for the rows of a batch of
+// which a CU holds six: a row's last round of pieces then wastes less (32
+// pairs of 640x480: 142 us with four, 165 with eight; 8 pairs of 1280x720: 142
+// and 110).
+constexpr int kMatchThreads = 512;
+constexpr int kMatchBatchThreads[kMatchVariants] = {256, 512};
+
+template <class DD, bool NT>
+__device__ __forceinline__ int match_row(const Frame& F, const Geometry& g, const KParams& p,
+                                         int v, int32_t* s_lut, int64_t* checking) {
+  constexpr int kStage = 3;  // columns of each view per thread and staging step
+  const int T = (int)blockDim.x, kWaves = T >> 6;
+  const int32_t* lut = F.lut;
+  // fields copied to locals first, so that no pointer is selected by
+  // indexing the frame struct (which would put it in scratch memory)
+  const uint8_t* descL = F.descL;
+  const uint8_t* descR = F.descR;
+  const int16_t* dplL = F.dplaneL;
+  const int16_t* dplR = F.dplaneR;
+  const uint32_t* gridL = F.gridL;
+  const uint32_t* gridR = F.gridR;
+  const int32_t* grL = F.grangeL;
+  const int32_t* grR = F.grangeR;
+  int16_t* rawL = F.rawL;
+  int16_t* rawR = F.rawR;
+  const bool has_list = F.hdr->n[0] > 0;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wp64 = (g.w + 63) & ~63, pieces = wp64 >> 6;
+  const size_t row = (size_t)v * g.w;
+  typename DD::T* const stL = reinterpret_cast<typename DD::T*>(dyn_smem);
+  typename DD::T* const stR = stL + wp64;
+  int16_t* const resL = reinterpret_cast<int16_t*>(stR + wp64);
+  int16_t* const resR = resL + wp64;
+  const int crow = grid_div(v, g) * g.gw;
+  // a piece's prior and region bit range (from in-bounds addresses always)
+  auto fetch = [&](int piece, int* dp, int2* rng) {
+    const bool right = piece >= pieces;
+    const int u = min(((right ? piece - pieces : piece) << 6) + lane, g.w - 1);
+    const int16_t* dprow = (right ? dplR : dplL) + row;
+    if constexpr (NT)
+      *dp = __builtin_nontemporal_load(&dprow[(uint32_t)u]);
+    else
+      *dp = dprow[(uint32_t)u];
+    *rng = (reinterpret_cast<const int2*>(right ? grR : grL) + crow)[(uint32_t)grid_div(u, g)];
+  };
+  int dp;
+  int2 rng;
+  for (int c0 = 0; c0 < g.w; c0 += kStage * T) {
+    typename DD::T a[kStage], b[kStage];
+#pragma unroll
+    for (int k = 0; k < kStage; ++k) {
+      const uint32_t c = (uint32_t)min(c0 + k * T + tid, g.w - 1);
+      a[k] = DD::template load_col<NT>(descL + row * DD::kBytes, c);
+      b[k] = DD::template load_col<NT>(descR + row * DD::kBytes, c);
+    }
+    if (c0 == 0) fetch(wid, &dp, &rng);
+#pragma unroll
+    for (int k = 0; k < kStage; ++k) {
+      const int c = c0 + k * T + tid;
+      if (c < g.w) {
+        stL[c] = a[k];
+        stR[c] = b[k];
+      }
+    }
+  }
+  for (int i = tid; i < kLutSize; i += T) {
+    const int32_t x = lut[min(abs(i - kLutC), p.D - 1)];
+    s_lut[i] = (i <= 2 * kLutC ? x : 0) + p.lut_bias;
+  }
+  WinPrior wp;
+  wp.p0 = (uint32_t)(lut[0] + p.lut_bias);
+  wp.p1 = (uint32_t)(lut[min(1, p.D - 1)] + p.lut_bias);
+  wp.p2 = (uint32_t)(lut[min(2, p.D - 1)] + p.lut_bias);
+  __syncthreads();
+  const bool vin = v >= 2 && v <= g.h - 3;
+  int cnt = 0;
+  for (int piece = wid; piece < 2 * pieces; piece += kWaves) {
+    const bool right = piece >= pieces;
+    const int u = ((right ? piece - pieces : piece) << 6) + lane;
+    const int cdp = dp;
+    const int2 crng = rng;
+    if (piece + kWaves < 2 * pieces) fetch(piece + kWaves, &dp, &rng);
+    int res = -1;
+    if (vin && u >= 2 && u <= g.w - 3) {
+      const size_t cell = (size_t)(crow + grid_div(u, g)) * g.gwords;
+      if (right)
+        res = dense_pixel<DD, true>(g, p, u, cdp, crng.x, crng.y, gridR + cell, has_list, stR[u],
+                                    stL, 0, s_lut, wp, &cnt);
+      else
+        res = dense_pixel<DD, false>(g, p, u, cdp, crng.x, crng.y, gridL + cell, has_list, stL[u],
+                                     stR, 0, s_lut, wp, &cnt);
+    }
+    if (right)
+      resR[u] = (int16_t)res;
+    else
+      resL[u] = (int16_t)res;
+  }
+  __syncthreads();
+  *checking = clock64();
+  // the check (e >= 0 and |e - d| <= threshold as one unsigned range test)
+  int16_t* outL = F.outL;
+  int16_t* outR = F.outR;
+  int16_t* chkL = F.chkL;
+  int16_t* chkR = F.chkR;
+  const int t = min(p.lr_threshold, 1 << 12);
+  for (int piece = wid; piece < 2 * pieces; piece += kWaves) {
+    const bool right = piece >= pieces;
+    const int u = ((right ? piece - pieces : piece) << 6) + lane;
+    if (u >= g.w) continue;
+    const int16_t* self = right ? resR : resL;
+    const int16_t* other = right ? resL : resR;
+    const int d = self[u], x = right ? u + d : u - d;
+    const int e = other[min(max(x, 0), g.w - 1)];
+    const int lo = max(0, d - t);
+    const bool ok = d >= 0 && x >= 0 && x < g.w && (uint32_t)(e - lo) <= (uint32_t)(d + t - lo);
+    const int16_t res = (int16_t)(ok ? d : -1);
+    __builtin_nontemporal_store((int16_t)d, (right ? rawR : rawL) + row + u);
+    if (p.median)
+      ((right ? chkR : chkL) + row)[u] = res;
+    else
+      __builtin_nontemporal_store(res, (right ? outR : outL) + row + u);
+  }
+  return cnt;
+}
+
+template <bool NT>
+__device__ __forceinline__ void match_rows(const Frame& F, int lb) {
+  __shared__ int32_t s_lut[kLutSize];  // mirrored prior table, then zeros
+  __shared__ int s_cnt[kMatchThreads / 64];
+  const Geometry g = F.g;
+  const KParams p = F.p;
+  const int64_t begin = clock64();
+  int64_t checking;
+  int cnt = p.descriptor ? match_row<CensusDense, NT>(F, g, p, lb, s_lut, &checking)
+                         : match_row<GradDense, NT>(F, g, p, lb, s_lut, &checking);
+  cnt = wave_sum_i32(cnt);
+  if ((threadIdx.x & 63) == 0) s_cnt[threadIdx.x >> 6] = cnt;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int sum = 0;
+    for (int w = 0; w < (int)blockDim.x >> 6; ++w) sum += s_cnt[w];
+    F.dense_counts[lb] = sum;
+    // the check's share of the row's time, for the stage times
+    const float end = (float)(clock64() - begin);
+    F.dense_counts[g.h + lb] = (int)(65536.f * (1.f - (float)(checking - begin) / end));
+  }
+}
+__device__ __forceinline__ void match_body(const Frame& F, int lb) { match_rows<false>(F, lb); }
+__device__ __forceinline__ void match_nt_body(const Frame& F, int lb) { match_rows<true>(F, lb); }
+
+// ---------------------------------------------------------------------------
 // Median post-filter (Section VIII) of the checked maps, window 3 or 5
 // clipped to the image: an invalid pixel stays invalid, a valid one takes
 // the lower median of the valid values in its window. Block = 64 x 4 pixels
@@ -2091,7 +2272,7 @@ ELAS_STAGE_KERNELS(k_support, support_body, 256)
 ELAS_FRAME_KERNEL_ATTR(k_filter, filter_body<1024>, 1024, ELAS_NO_ATTR)
 ELAS_BATCH_KERNEL_ATTR(k_filter, filter_body<512>, 512, ELAS_NO_ATTR)
 ELAS_STAGE_KERNELS(k_rows, rows_body, 64)
-ELAS_STAGE_KERNELS(k_raster, raster_body<1024>, 1024)
+ELAS_FRAME_KERNEL_ATTR(k_raster, raster_body<1024>, 1024, ELAS_NO_ATTR)
 ELAS_STAGE_KERNELS(k_raster256, raster_body<256>, 256)
 ELAS_STAGE_KERNELS_ATTR(k_dense_r1, dense_body<1>, 256, ELAS_OCC8)
 ELAS_STAGE_KERNELS_ATTR(k_dense_r2, dense_body<2>, 256, ELAS_OCC8)
@@ -2100,6 +2281,8 @@ ELAS_BATCH_KERNEL_ATTR(k_dense_r1nt, dense_nt_body<1>, 256, ELAS_OCC8)
 ELAS_BATCH_KERNEL_ATTR(k_dense_r2nt, dense_nt_body<2>, 256, ELAS_OCC8)
 ELAS_BATCH_KERNEL_ATTR(k_dense_r4nt, dense_nt_body<4>, 256, ELAS_NO_ATTR)
 ELAS_STAGE_KERNELS(k_check, check_body, 256)
+ELAS_STAGE_KERNELS(k_match, match_body, kMatchThreads)
+ELAS_BATCH_KERNEL_ATTR(k_matchnt, match_nt_body, kMatchThreads, ELAS_NO_ATTR)
 ELAS_STAGE_KERNELS(k_redun, redun_body, 1024)
 ELAS_STAGE_KERNELS(k_median, median_body, 256)
 
@@ -2120,6 +2303,7 @@ int stage_threads(int32_t stage) {
   switch (stage) {
     case kStageFilter: return 512;  // the batched launch; single frames take 1024
     case kStageRedun: return 1024;
+    case kStageMatch: return kMatchThreads;  // batches choose by variant
     case kStageRows: return 64;
     case kStageRaster: return 256;  // the batched launch; single frames choose in launch_stage
     default: return 256;
@@ -2137,6 +2321,12 @@ int32_t dense_blocks(const Geometry& g, int variant) {
 
 int32_t dense_blocks_max(const Geometry& g) { return dense_blocks(g, 0); }
 
+bool match_fused(const Geometry& g, const KParams& p) { return match_lds(g, p) <= kMatchLds; }
+
+int match_variant(const Geometry& g, const KParams& p) {
+  return 6 * (match_lds(g, p) + 4096) <= 160 * 1024 ? 0 : 1;  // 4 KB: the static part
+}
+
 int32_t stage_blocks(int32_t stage, const Geometry& g, const KParams& p, int dv) {
   switch (stage) {
     case kStageDescriptor:
@@ -2148,8 +2338,10 @@ int32_t stage_blocks(int32_t stage, const Geometry& g, const KParams& p, int dv)
     case kStageMesh:
     case kStageTris: return mesh_blocks(stage, g, true);
     case kStageRaster: return 2 * cdiv(g.h, raster_band_rows(g.w));
-    case kStageDense: return dense_blocks(g, dv);
-    case kStageCheck: return 2 * cdiv((long long)g.w * g.h, 256 * kCheckPx);
+    case kStageDense: return match_fused(g, p) ? 0 : dense_blocks(g, dv);
+    case kStageCheck:
+      return match_fused(g, p) ? 0 : 2 * cdiv((long long)g.w * g.h, 256 * kCheckPx);
+    case kStageMatch: return match_fused(g, p) ? g.h : 0;
     case kStageMedian: return p.median ? 2 * cdiv(g.w, kMedW) * cdiv(g.h, kMedH) : 0;
     default: return 0;
   }
@@ -2160,6 +2352,7 @@ size_t stage_lds(int32_t stage, const Geometry& g, const KParams& p) {
     case kStageFilter: return filter_lds_bytes(g, p);
     case kStageRows: return sizeof(int32_t) * (size_t)g.w;
     case kStageRedun: return p.redundancy ? redun_lds(g) : 0;
+    case kStageMatch: return match_fused(g, p) ? match_lds(g, p) : 0;
     case kStageRaster: return sizeof(int32_t) * (size_t)raster_band_rows(g.w) * g.w;
     case kStageMesh: return mesh_lds(g);
     case kStageSupport: {
@@ -2216,6 +2409,7 @@ hipError_t launch_stage(int32_t stage, const Frame& f, int variant, hipStream_t 
         go(k_dense_r2);
       break;
     case kStageCheck: go(k_check); break;
+    case kStageMatch: go(k_match); break;
     case kStageMedian: go(k_median); break;
     default: return hipErrorInvalidValue;
   }
@@ -2243,7 +2437,8 @@ hipError_t launch_stage_batch(int32_t stage, const Frame* frames, const int32_t*
   const uint32_t bmul = bpf ? (uint32_t)(((1ull << 32) + (uint64_t)bpf - 1) / (uint64_t)bpf) : 0u;
   if (stage == kStageMesh || stage == kStageTris)
     return launch_mesh_batch(stage, frames, starts, nf, total_blocks, bpf, bmul, lds, s, start, stop);
-  const dim3 grid(total_blocks), block(stage_threads(stage));
+  const dim3 grid(total_blocks),
+      block(stage == kStageMatch ? kMatchBatchThreads[variant] : stage_threads(stage));
   const uint32_t shm = (uint32_t)lds;
   const bool timed = start || stop;
   auto go = [&](auto kernel, uint32_t bytes) {
@@ -2275,6 +2470,7 @@ hipError_t launch_stage_batch(int32_t stage, const Frame* frames, const int32_t*
         desc_nt ? go(k_dense_r2nt_batch, 0u) : go(k_dense_r2_batch, 0u);
       break;
     case kStageCheck: go(k_check_batch, 0u); break;
+    case kStageMatch: desc_nt ? go(k_matchnt_batch, shm) : go(k_match_batch, shm); break;
     case kStageRedun: go(k_redun_batch, shm); break;
     case kStageMedian: go(k_median_batch, 0u); break;
     default: return hipErrorInvalidValue;
