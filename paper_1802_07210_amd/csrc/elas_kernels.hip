@@ -33,8 +33,8 @@ __device__ __forceinline__ uint4 ld16(const uint8_t* p) {
   return *reinterpret_cast<const uint4*>(p);
 }
 
-__device__ __forceinline__ uint32_t sad16(const uint4 a, const uint4 b) {
-  uint32_t s = __builtin_amdgcn_sad_u8(a.x, b.x, 0u);
+__device__ __forceinline__ uint32_t sad16(const uint4 a, const uint4 b, uint32_t s) {
+  s = __builtin_amdgcn_sad_u8(a.x, b.x, s);
   s = __builtin_amdgcn_sad_u8(a.y, b.y, s);
   s = __builtin_amdgcn_sad_u8(a.z, b.z, s);
   return __builtin_amdgcn_sad_u8(a.w, b.w, s);
@@ -42,7 +42,7 @@ __device__ __forceinline__ uint32_t sad16(const uint4 a, const uint4 b) {
 
 // Texture: distance of a descriptor from the flat descriptor (all bytes 128).
 __device__ __forceinline__ uint32_t texture16(const uint4 a) {
-  return sad16(a, make_uint4(0x80808080u, 0x80808080u, 0x80808080u, 0x80808080u));
+  return sad16(a, make_uint4(0x80808080u, 0x80808080u, 0x80808080u, 0x80808080u), 0u);
 }
 
 // Workgroups are dispatched to the 8 XCDs round-robin (block b runs on XCD
@@ -370,12 +370,12 @@ __device__ __forceinline__ void stage1_nt_body(const Frame& F, int lb) {
 
 // ---------------------------------------------------------------------------
 // Stage 2: support matching (Section III-A) with a reverse check. A
-// workgroup takes a run of up to 16 lattice points on one lattice row and
-// stages, once, every descriptor column its searches can reach (both views,
-// the rows the support descriptor samples) in LDS; each wavefront then takes
-// every fourth point of the run, lane k evaluating d = dmin + k + 64 j with
-// its candidates read from LDS and the point's own descriptor from scalar
-// loads (one address for the whole wavefront).
+// workgroup takes a run of lattice points on one lattice row and stages, once,
+// every descriptor column its searches can reach (both views, the rows the
+// support descriptor samples) in LDS; each wavefront then takes groups of four
+// (short runs: two) neighbouring points, lane k evaluating d = dmin + k + 64 j
+// of each with its candidates read from LDS and the point's own descriptor
+// from scalar loads (one address for the whole wavefront).
 // Ambiguity test: eq. 1-2 (m1 < t*m2 in FP32) or the shift-sum of eq. 3
 // (m1 <= m2/2 + m2/4 + m2/8 + m2/32 with truncating shifts). Descriptors:
 //  * gradient: the 512-bit support descriptor is the four 16-byte descriptors
@@ -383,15 +383,6 @@ __device__ __forceinline__ void stage1_nt_body(const Frame& F, int lb) {
 //  * census: the support-window census of the pixel; cost = Hamming distance;
 //    texture = number of set bits.
 // ---------------------------------------------------------------------------
-struct Desc64 {
-  uint4 q[4];
-};
-
-__device__ __forceinline__ uint32_t sad64(const Desc64& a, const Desc64& b) {
-  return sad16(a.q[0], b.q[0]) + sad16(a.q[1], b.q[1]) + sad16(a.q[2], b.q[2]) +
-         sad16(a.q[3], b.q[3]);
-}
-
 __device__ __forceinline__ bool support_accept(const KParams& p, uint32_t m1, uint32_t m2) {
   if (p.ambiguity) return m1 <= (m2 >> 1) + (m2 >> 2) + (m2 >> 3) + (m2 >> 5);
   return (float)m1 < __fmul_rn(p.support_threshold, (float)m2);
@@ -404,26 +395,26 @@ __device__ __forceinline__ uint4 xor4(const uint4 a, const uint4 b) {
   return make_uint4(a.x ^ b.x, a.y ^ b.y, a.z ^ b.z, a.w ^ b.w);
 }
 
-// A census support descriptor: NQ 16-byte words; cost = Hamming distance.
-template <int NQ>
-struct CensusDesc {
-  uint4 q[NQ];
+// A part of a support descriptor, what one LDS plane holds of it (the
+// searches add up the costs part by part): two of the four gradient
+// descriptors, or one 16-byte word of the census.
+struct GradPart {
+  uint4 q[2];
 };
-template <int NQ>
-__device__ __forceinline__ uint32_t hamming(const CensusDesc<NQ>& a, const CensusDesc<NQ>& b) {
-  uint32_t c = 0;
-#pragma unroll
-  for (int i = 0; i < NQ; ++i) c += popc4(xor4(a.q[i], b.q[i]));
-  return c;
+__device__ __forceinline__ uint32_t add_cost(uint32_t c, const GradPart& a, const GradPart& b) {
+  return sad16(a.q[1], b.q[1], sad16(a.q[0], b.q[0], c));
+}
+__device__ __forceinline__ uint32_t add_cost(uint32_t c, const uint4& a, const uint4& b) {
+  return c + popc4(xor4(a, b));
 }
 
 // LDS copies of a view's descriptor columns c0.. (one plane of 16 bytes per
 // column for each descriptor row or census word), the sources of the
-// searches: load(x) = the descriptor of column x on the point's row (the
-// gradient descriptor takes columns x - 2 and x + 2 of rows v - 2 and
-// v + 2); cost(a, b). texture(x, lane) splits the point's own texture over the
+// searches: load(at(x), h) = part h of the descriptor of column x on the
+// point's row (the gradient descriptor takes columns x - 2 and x + 2 of rows
+// v - 2 and v + 2). texture(x, lane) splits the point's own texture over the
 // lanes of each 16-lane row: lane i takes 4 of its bytes, a row sum adds
-// them, so the wavefront pays one SAD instead of sixteen.
+// them, so each row can judge a point of its own with one SAD for all.
 __device__ __forceinline__ uint4 lds16(uint32_t off) {
   return *reinterpret_cast<const uint4*>(dyn_smem + off);
 }
@@ -431,20 +422,28 @@ __device__ __forceinline__ uint32_t lds4(uint32_t off) {
   return *reinterpret_cast<const uint32_t*>(dyn_smem + off);
 }
 
+// 16 bytes per lane from memory to LDS at off + 16 * lane (off the same in the
+// whole wavefront); nothing may read them before wait_lds_loads and, in other
+// wavefronts, a barrier after it.
+__device__ __forceinline__ void load_lds16(const uint8_t* src, uint32_t off) {
+  typedef __attribute__((address_space(1))) const void* Global;
+  typedef __attribute__((address_space(3))) void* Lds;
+  __builtin_amdgcn_global_load_lds((Global)src, (Lds)(dyn_smem + off), 16, 0, 0);
+}
+__device__ __forceinline__ void wait_lds_loads() {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
 struct LdsGrad {
-  typedef Desc64 T;
-  __device__ __forceinline__ static uint32_t cost(const T& a, const T& b) { return sad64(a, b); }
+  typedef GradPart T;
+  static constexpr int kParts = 2;
   uint32_t base;     // plane 0: row v - 2; plane 1 (base + pstride): row v + 2
   uint32_t pstride;
   int c0;
-  __device__ __forceinline__ T load(int x) const {
-    const uint32_t o = base + (uint32_t)(x - 2 - c0) * 16u;  // columns x - 2 and x + 2
-    Desc64 r;
-    r.q[0] = lds16(o);
-    r.q[1] = lds16(o + 64u);
-    r.q[2] = lds16(o + pstride);
-    r.q[3] = lds16(o + pstride + 64u);
-    return r;
+  __device__ __forceinline__ uint32_t at(int x) const { return base + (uint32_t)(x - 2 - c0) * 16u; }
+  __device__ __forceinline__ T load(uint32_t at, int h) const {
+    const uint32_t o = at + (h ? pstride : 0u);  // columns x - 2 and x + 2
+    return T{{lds16(o), lds16(o + 64u)}};
   }
   // lane i of a row: dword i & 3 of part (i >> 2) & 3 of the descriptor
   __device__ __forceinline__ uint32_t texture(int x, int lane) const {
@@ -452,23 +451,20 @@ struct LdsGrad {
     const uint32_t o = base + (uint32_t)(x - 2 - c0) * 16u + (uint32_t)(part & 1) * 64u +
                        (uint32_t)(part >> 1) * pstride + (uint32_t)(lane & 3) * 4u;
     const uint32_t t = __builtin_amdgcn_sad_u8(lds4(o), 0x80808080u, 0u);
-    return (uint32_t)__builtin_amdgcn_readfirstlane((int)row_sum_u32(t));
+    return row_sum_u32(t);
   }
 };
 
 template <int NQ>
 struct LdsCensus {
-  typedef CensusDesc<NQ> T;
-  __device__ __forceinline__ static uint32_t cost(const T& a, const T& b) { return hamming(a, b); }
+  typedef uint4 T;
+  static constexpr int kParts = NQ;
   uint32_t base;     // plane i (base + i * pstride): word i of each column
   uint32_t pstride;
   int c0;
-  __device__ __forceinline__ T load(int x) const {
-    const uint32_t o = base + (uint32_t)(x - c0) * 16u;
-    T r;
-#pragma unroll
-    for (int i = 0; i < NQ; ++i) r.q[i] = lds16(o + (uint32_t)i * pstride);
-    return r;
+  __device__ __forceinline__ uint32_t at(int x) const { return base + (uint32_t)(x - c0) * 16u; }
+  __device__ __forceinline__ T load(uint32_t at, int h) const {
+    return lds16(at + (h ? pstride : 0u));
   }
   // lane i < 4 NQ of a row: the set bits of dword i & 3 of word i >> 2
   __device__ __forceinline__ uint32_t texture(int x, int lane) const {
@@ -476,132 +472,246 @@ struct LdsCensus {
     const uint32_t o = base + (uint32_t)(x - c0) * 16u + (uint32_t)wd * pstride +
                        (uint32_t)(i & 3) * 4u;
     const uint32_t t = i < 4 * NQ ? (uint32_t)__popc(lds4(o)) : 0u;
-    return (uint32_t)__builtin_amdgcn_readfirstlane((int)row_sum_u32(t));
+    return row_sum_u32(t);
   }
 };
 
 // The point's own descriptor in global memory, one address for the whole
 // wavefront: scalar loads into SGPRs, which each SAD takes as its scalar
-// operand (no LDS bandwidth and no VGPRs for it).
+// operand (no LDS bandwidth and no VGPRs for it). The constant address space
+// says what holds of this kernel: nothing in it writes descriptors.
+__device__ __forceinline__ uint4 uniform16(const uint8_t* p) {
+  typedef uint32_t V __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(4))) const V* Ptr;
+  const V v = *(Ptr)(uintptr_t)p;
+  return make_uint4(v.x, v.y, v.z, v.w);
+}
 struct GradSelf {
   const uint8_t* ra;  // row v - 2
   const uint8_t* rb;  // row v + 2
-  __device__ __forceinline__ Desc64 load(int x) const {
-    const uint32_t o = (uint32_t)(x - 2) * 16u;  // columns x - 2 and x + 2
-    Desc64 r;
-    r.q[0] = ld16(ra + o);
-    r.q[1] = ld16(ra + o + 64u);
-    r.q[2] = ld16(rb + o);
-    r.q[3] = ld16(rb + o + 64u);
-    return r;
+  __device__ __forceinline__ GradPart load(int x, int h) const {
+    const uint8_t* const o = (h ? rb : ra) + (uint32_t)(x - 2) * 16u;  // columns x - 2 and x + 2
+    return GradPart{{uniform16(o), uniform16(o + 64)}};
   }
 };
 
 template <int NQ>
 struct CensusSelf {
-  const uint4* row;  // the lattice row's census, NQ words per column
-  __device__ __forceinline__ CensusDesc<NQ> load(int x) const {
-    CensusDesc<NQ> r;
-#pragma unroll
-    for (int i = 0; i < NQ; ++i) r.q[i] = row[(uint32_t)x * NQ + i];
-    return r;
+  const uint8_t* row;  // the lattice row's census, NQ 16-byte words per column
+  __device__ __forceinline__ uint4 load(int x, int h) const {
+    return uniform16(row + ((uint32_t)x * NQ + (uint32_t)h) * 16u);
   }
 };
 
-// One search of a point with own descriptor `self`: the candidate columns
-// u + dir*d, d = dmin + lane + 64 j for j < NJ (NJ 64-wide batches cover the
-// disparity range), taken two batches at a time so that at most two
-// candidate descriptors per lane are live. Lanes past dhi load column dhi
-// instead (in the image like every searched column) and are masked out.
-// FULL: every lane of every batch is in range (dhi = dmin + 64 NJ - 1), so a
-// batch's columns are one lane-dependent base plus constants and its loads
-// take immediate offsets. Argmin over d = dmin..dhi (smallest cost, smallest
-// d on ties; at least two values) and the ambiguity test; returns whether it
-// accepts. Control flow is wavefront-uniform.
-template <int NJ, bool FULL, class C>
-__device__ __forceinline__ bool search(const typename C::T& self, const C& other, int u, int dir,
-                                       int dhi, const KParams& p, int lane, int* d_best) {
-  uint32_t key[NJ];
-  uint32_t best = 0xFFFFFFFFu;
-  const int xb = dir < 0 ? u - p.dmin - lane : u + p.dmin + lane;  // column of batch 0
+// The two smallest keys of a set; keys are distinct (their low byte is the
+// disparity).
+struct Two {
+  uint32_t a, b;  // a <= b
+};
+__device__ __forceinline__ Two two_of(const Two& x, const Two& y) {
+  return Two{min(x.a, y.a), min(min(max(x.a, y.a), x.b), y.b)};
+}
+// b = median(a, b, key), a = min(a, key): the third operand of the median
+// keeps it one instruction per key
+__device__ __forceinline__ void two_add(Two* t, uint32_t key) {
+  uint32_t b;
+  asm("v_med3_u32 %0, %1, %2, %3" : "=v"(b) : "v"(t->a), "v"(t->b), "v"(key));
+  t->b = b;
+  t->a = min(t->a, key);
+}
+template <int kCtl>
+__device__ __forceinline__ Two two_row(const Two& t) {
+  return two_of(t, Two{dpp_full<kCtl>(t.a), dpp_full<kCtl>(t.b)});
+}
+// Lanes 0..31 of the result reduce x over its halves, lanes 32..63 y.
+__device__ __forceinline__ Two two_halves(const Two& x, const Two& y) {
+  const auto a = __builtin_amdgcn_permlane32_swap(x.a, y.a, false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap(x.b, y.b, false, false);
+  return two_of(Two{a[0], b[0]}, Two{a[1], b[1]});
+}
+// Rows 0 and 2 of the result reduce x over rows (0, 1) and (2, 3), rows 1 and
+// 3 y.
+__device__ __forceinline__ Two two_rows(const Two& x, const Two& y) {
+  const auto a = __builtin_amdgcn_permlane16_swap(x.a, y.a, false, false);
+  const auto b = __builtin_amdgcn_permlane16_swap(x.b, y.b, false, false);
+  return two_of(Two{a[0], b[0]}, Two{a[1], b[1]});
+}
+
+// The searches of G points (4 or 2) by one wavefront: point i with own
+// descriptor at column u[i] over d = dmin + kk, kk = 0..nd[i]
+// (nd >= 1 for a result that means anything), the candidate columns u + dir*d;
+// lane l takes kk = l + 64 j in step j < NJ. Returns, in every lane of 16-lane
+// row r, the two smallest (cost << 8 | kk) of point r (G = 4) or r / 2 (G = 2)
+// - the smallest cost, the smallest disparity on ties, and the second smallest
+// cost. The G reductions over the lanes share their steps: half of the lanes
+// go on with one point, half with another, from the first step on, and what
+// follows (thresholds, texture, results) judges G points in one instruction.
+// The kernel is bound by its vector instructions (four fifths of the issue
+// slots); of them the 16 SADs a candidate needs are under half. One point at a
+// time took 55.7 M instructions for 8 pairs of 1280x720 at 192 disparities and
+// 126 us; four at a time 51.8 M and 112 (8 pairs of 640x480: 38.5 and 35.3; one
+// frame of 1242x375: 16.8 and 14.5). Sharing the candidates' LDS reads among
+// the four (their columns overlap) was no gain: it costs scalar registers,
+// and the LDS reads are not the bound.
+// FULL: every lane of every step is in range for every point.
+template <int NJ, int G, int DIR, bool FULL, class GS, class C>
+__device__ __forceinline__ Two search(const GS& self, const C& other, const int (&u)[G],
+                                      const int (&nd)[G], const KParams& p, int lane) {
+  constexpr int kP = C::kParts;
+  Two best[G];
 #pragma unroll
-  for (int j0 = 0; j0 < NJ; j0 += 2) {
-    typename C::T o[2];
+  for (int i = 0; i < G; ++i) {
+    typename C::T own[kP];
 #pragma unroll
-    for (int jj = 0; jj < 2 && j0 + jj < NJ; ++jj) {
-      const int j = j0 + jj;
-      o[jj] = other.load(FULL ? xb + dir * 64 * j : u + dir * min(p.dmin + lane + 64 * j, dhi));
+    for (int h = 0; h < kP; ++h) own[h] = self.load(u[i], h);
+    // kk = 0 (in the staged columns even where nd < 0); FULL: the lowest
+    // column of the lane's steps (64 apart)
+    const uint32_t zero = other.at(DIR < 0 ? max(u[i] - p.dmin, 4) : u[i] + p.dmin);
+    const uint32_t low = zero + (uint32_t)(DIR < 0 ? -16 * lane - 1024 * (NJ - 1) : 16 * lane);
+    const uint32_t last = 16u * (uint32_t)max(nd[i], 0);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const int kk = lane + 64 * j;
+      const uint32_t at =
+          FULL ? low + 1024u * (DIR < 0 ? NJ - 1 - j : j)
+               : zero + (uint32_t)DIR * min(16u * (uint32_t)kk, last);
+      uint32_t c = 0;
+#pragma unroll
+      for (int h = 0; h < kP; ++h) c = add_cost(c, own[h], other.load(at, h));
+      const uint32_t key = FULL || kk <= nd[i] ? (c << 8) | (uint32_t)kk : 0xFFFFFFFFu;
+      if (j == 0)
+        best[i] = Two{key, 0xFFFFFFFFu};
+      else
+        two_add(&best[i], key);
     }
+    __builtin_amdgcn_sched_barrier(0);  // few candidates live at a time: more wavefronts
+  }
+  Two t;
+  if constexpr (G == 4) {
+    t = two_rows(two_halves(best[0], best[2]), two_halves(best[1], best[3]));
+  } else {
+    t = two_halves(best[0], best[1]);
+    t = two_rows(t, t);
+  }
+  t = two_row<kDppQuadXor1>(t);
+  t = two_row<kDppQuadXor2>(t);
+  t = two_row<kDppRowHalfMirror>(t);
+  return two_row<kDppRowMirror>(t);
+}
+
+// x[i] in every lane of row r, i = r (G = 4) or r / 2 (G = 2). By masks: a
+// choice between elements would be turned into one of their addresses, which
+// puts the array into scratch memory.
+template <int G>
+__device__ __forceinline__ int of_row(const int (&x)[G], int lane) {
+  const int hi = -(lane >> 5);
+  if constexpr (G == 2) {
+    return x[0] ^ ((x[0] ^ x[1]) & hi);
+  } else {
+    const int odd = -((lane >> 4) & 1);
+    const int a = x[0] ^ ((x[0] ^ x[1]) & odd), b = x[2] ^ ((x[2] ^ x[3]) & odd);
+    return a ^ ((a ^ b) & hi);
+  }
+}
+
+// Reverse searches of up to G accepted points of a group of F: bit i of `todo`
+// is the group's point i (at least one, at most G set), whose right column ur
+// and matched disparity d1 are in lanes 64 / F * i and following.
+template <int NJ, int F, int G, class GS, class C>
+__device__ __forceinline__ void support_reverse(const GS& gR, const C& cL, const C& cR,
+                                                uint32_t todo, int d1, int ur, int w,
+                                                const KParams& p, int lane, int32_t* s_res,
+                                                int32_t* s_ev) {
+  int at[G], x[G], nd[G];
+  bool full = true;
+  const int slots = __popc(todo);
 #pragma unroll
-    for (int jj = 0; jj < 2 && j0 + jj < NJ; ++jj) {
-      const int j = j0 + jj, k = lane + 64 * j;  // k = d - dmin
-      const uint32_t c = C::cost(self, o[jj]);
-      key[j] = FULL || p.dmin + k <= dhi ? (c << 8) | (uint32_t)k : 0xFFFFFFFFu;
-      best = min(best, key[j]);
+  for (int i = 0; i < G; ++i) {
+    at[i] = __ffs((int)todo) - 1;
+    if (todo & (todo - 1u)) todo &= todo - 1u;  // the last point fills the rest
+    x[i] = __builtin_amdgcn_readlane(ur, 64 / F * at[i]);
+    nd[i] = min(p.dmax, w - 5 - x[i]) - p.dmin;
+    full &= nd[i] == 64 * NJ - 1;
+  }
+  const Two t = full ? search<NJ, G, +1, true>(gR, cL, x, nd, p, lane)
+                     : search<NJ, G, +1, false>(gR, cL, x, nd, p, lane);
+  const int point = of_row<G>(at, lane), xr = of_row<G>(x, lane), n = of_row<G>(nd, lane) + 1;
+  const int df = __shfl(d1, 64 / F * point);
+  const bool textured = (int)cR.texture(xr, lane) >= p.support_texture;
+  const int d2 = p.dmin + (int)(t.a & 0xFFu);
+  const bool ok = textured && support_accept(p, t.a >> 8, t.b >> 8) && abs(d2 - df) <= p.lr_threshold;
+  constexpr int kL = 64 / G;  // lanes that judge one point
+  if ((lane & (kL - 1)) == 0 && lane / kL < slots) {
+    if (ok) s_res[point] = df;
+    if (textured) s_ev[point] += n;
+  }
+}
+
+// A group of F consecutive lattice points (from k; those at or after k1 are
+// repeats of k1 - 1 and write nothing): forward searches of all, then reverse
+// searches, from the matched right columns, of those accepted. gL, gR: the
+// views in global memory (the own descriptors); cL, cR: the staged columns in
+// LDS (candidates, texture). 64 / F lanes judge each point.
+template <int NJ, int F, class GS, class C>
+__device__ __forceinline__ void support_group(const GS& gL, const GS& gR, const C& cL, const C& cR,
+                                              const Geometry& g, const KParams& p, int k, int k1,
+                                              int lane, int32_t* s_res, int32_t* s_ev) {
+  constexpr int kL = 64 / F;
+  int u[F], nd[F];
+#pragma unroll
+  for (int i = 0; i < F; ++i) {
+    u[i] = g.lu0 + min(k + i, k1 - 1) * g.step;
+    nd[i] = min(p.dmax, u[i] - 4) - p.dmin;
+  }
+  const Two t = nd[0] == 64 * NJ - 1 ? search<NJ, F, -1, true>(gL, cR, u, nd, p, lane)
+                                     : search<NJ, F, -1, false>(gL, cR, u, nd, p, lane);
+  const int ul = of_row<F>(u, lane), n = of_row<F>(nd, lane) + 1, i = lane / kL;
+  const bool textured = n >= 2 && (int)cL.texture(ul, lane) >= p.support_texture;
+  const int d1 = p.dmin + (int)(t.a & 0xFFu), ur = ul - d1;
+  const bool ok = textured && k + i < k1 && support_accept(p, t.a >> 8, t.b >> 8) &&
+                  min(p.dmax, g.w - 5 - ur) - p.dmin >= 1;
+  if ((lane & (kL - 1)) == 0 && k + i < k1) {
+    s_res[i] = -1;
+    s_ev[i] = textured ? n : 0;
+  }
+  const unsigned long long m = __builtin_amdgcn_ballot_w64(ok);
+  uint32_t todo = 0;
+#pragma unroll
+  for (int q = 0; q < F; ++q) todo |= (uint32_t)(m >> (kL * q) & 1) << q;
+  if (F == 4 && __popc(todo) > 2)
+    support_reverse<NJ, F, F>(gR, cL, cR, todo, d1, ur, g.w, p, lane, s_res, s_ev);
+  else if (todo)
+    support_reverse<NJ, F, 2>(gR, cL, cR, todo, d1, ur, g.w, p, lane, s_res, s_ev);
+}
+
+// The run's groups, one per wavefront in turn, with the step count of the
+// frame's disparity range as a template argument.
+template <int F, class GS, class C>
+__device__ __forceinline__ void support_groups(const GS& gL, const GS& gR, const C& cL,
+                                               const C& cR, const Geometry& g, const KParams& p,
+                                               int k0, int k1, int wv, int lane, int32_t* s_res,
+                                               int32_t* s_ev) {
+  for (int k = k0 + F * wv; k < k1; k += 4 * F) {
+    int32_t* const r = s_res + (k - k0);
+    int32_t* const e = s_ev + (k - k0);
+    switch ((p.D + 63) >> 6) {
+      case 1: support_group<1, F>(gL, gR, cL, cR, g, p, k, k1, lane, r, e); break;
+      case 2: support_group<2, F>(gL, gR, cL, cR, g, p, k, k1, lane, r, e); break;
+      case 3: support_group<3, F>(gL, gR, cL, cR, g, p, k, k1, lane, r, e); break;
+      default: support_group<4, F>(gL, gR, cL, cR, g, p, k, k1, lane, r, e); break;
     }
   }
-  best = wave_min_u32(best);
-  const int d1 = p.dmin + (int)(best & 0xFFu);
-  const uint32_t m1 = best >> 8;
-  uint32_t m2 = 0xFFFFFFFFu;
-#pragma unroll
-  for (int j = 0; j < NJ; ++j) m2 = min(m2, key[j] != best ? key[j] : 0xFFFFFFFFu);
-  m2 = wave_min_u32(m2) >> 8;
-  *d_best = d1;
-  return support_accept(p, m1, m2);
 }
-
-// The search (full or general form) and the texture test. The search runs
-// whether or not the own descriptor is textured, so that its loads (scalar
-// and LDS) all issue at once instead of waiting behind the texture test's
-// branch; *d_best = -2 when the own descriptor is untextured (the search
-// does not count as evaluated and never accepts).
-template <int NJ, class G, class C>
-__device__ __forceinline__ bool support_search(const G& self_src, const C& self_lds, int xs,
-                                               const C& other, int u, int dir, int dhi,
-                                               const KParams& p, int lane, int* d_best) {
-  const typename C::T self = self_src.load(xs);
-  const bool textured = (int)self_lds.texture(xs, lane) >= p.support_texture;
-  const bool ok = dhi - p.dmin + 1 == 64 * NJ
-                      ? search<NJ, true>(self, other, u, dir, dhi, p, lane, d_best)
-                      : search<NJ, false>(self, other, u, dir, dhi, p, lane, d_best);
-  if (!textured) *d_best = -2;
-  return ok && textured;
-}
-
-// One lattice point: forward search, then the reverse search from the
-// matched right column. gL, gR: the views in global memory (the own
-// descriptors); cL, cR: the staged columns in LDS (candidates, texture).
-template <int NJ, class G, class C>
-__device__ __forceinline__ int support_point(const G& gL, const G& gR, const C& cL, const C& cR,
-                                             int u, int w, const KParams& p, int lane,
-                                             int* ev) {
-  const int dhi = min(p.dmax, u - 4);
-  if (dhi - p.dmin + 1 < 2) return -1;
-  int d1;
-  const bool fwd = support_search<NJ>(gL, cL, u, cR, u, -1, dhi, p, lane, &d1);
-  if (d1 != -2) *ev += dhi - p.dmin + 1;  // textured: the search was evaluated
-  if (!fwd) return -1;
-  const int ur = u - d1;
-  const int dhi2 = min(p.dmax, w - 5 - ur);
-  if (dhi2 - p.dmin + 1 < 2) return -1;
-  int d2;
-  const bool rev = support_search<NJ>(gR, cR, ur, cL, ur, +1, dhi2, p, lane, &d2);
-  if (d2 != -2) *ev += dhi2 - p.dmin + 1;
-  return rev && abs(d2 - d1) <= p.lr_threshold ? d1 : -1;
-}
-
-// The batch count of the frame's disparity range, as a template argument.
-template <class G, class C>
-__device__ __forceinline__ int support_point_d(const G& gL, const G& gR, const C& cL,
-                                               const C& cR, int u, int w, const KParams& p,
-                                               int lane, int* ev) {
-  switch ((p.D + 63) >> 6) {
-    case 1: return support_point<1>(gL, gR, cL, cR, u, w, p, lane, ev);
-    case 2: return support_point<2>(gL, gR, cL, cR, u, w, p, lane, ev);
-    case 3: return support_point<3>(gL, gR, cL, cR, u, w, p, lane, ev);
-    default: return support_point<4>(gL, gR, cL, cR, u, w, p, lane, ev);
-  }
+// Groups of four; of two in short runs, which give every wavefront one.
+template <class GS, class C>
+__device__ __forceinline__ void support_runs(const GS& gL, const GS& gR, const C& cL, const C& cR,
+                                             const Geometry& g, const KParams& p, int q, int k0,
+                                             int k1, int wv, int lane, int32_t* s_res,
+                                             int32_t* s_ev) {
+  if (q > 8)
+    support_groups<4>(gL, gR, cL, cR, g, p, k0, k1, wv, lane, s_res, s_ev);
+  else
+    support_groups<2>(gL, gR, cL, cR, g, p, k0, k1, wv, lane, s_res, s_ev);
 }
 
 // Columns a run of q lattice points (step apart) can reach, per view: right
@@ -616,7 +726,6 @@ __host__ __device__ __forceinline__ int support_cols_left(int q, int step, int D
 }
 constexpr int kSupportRunMax = 32;          // lattice points per workgroup, at most
 constexpr int kSupportLdsMax = 64 * 1024;   // 32 bytes per staged column
-constexpr int kSupportStageCols = 512;      // columns per plane staged per round
 
 // Points per workgroup: the geometry's run length, fewer when the staged
 // columns would not fit.
@@ -661,55 +770,35 @@ __device__ __forceinline__ void support_body(const Frame& F, int lb) {
       pb[k] = reinterpret_cast<const uint8_t*>((right ? F.csupR : F.csupL) +
                                                ((size_t)l * g.w + c0) * p.cs_q + pl);
   }
-  const int nmax = max(nR, nL);
-  for (int c0 = 0; c0 < nmax; c0 += kSupportStageCols) {
-    uint4 t[4][kSupportStageCols / 256];
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-#pragma unroll
-      for (int s2 = 0; s2 < kSupportStageCols / 256; ++s2) {
-        const int c = min(c0 + s2 * 256 + tid, max(pn[k], 1) - 1);
-        t[k][s2] = ld16(pb[k] + (uint32_t)c * pitch);
-      }
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-#pragma unroll
-      for (int s2 = 0; s2 < kSupportStageCols / 256; ++s2) {
-        const int c = c0 + s2 * 256 + tid;
-        if (c < pn[k]) *reinterpret_cast<uint4*>(dyn_smem + pd[k] + (uint32_t)c * 16u) = t[k][s2];
-      }
-  }
-  __syncthreads();
-  // results go through LDS and out in one coalesced store per block: with no
-  // global store in the kernel before them, the loads of each point's own
-  // descriptor are known not to be clobbered and become scalar loads
-  __shared__ int32_t s_res[kSupportRunMax], s_ev[kSupportRunMax];
+  // straight from memory to LDS: a wavefront's load puts 64 columns of a plane
+  // behind one another, which is the plane's layout, and takes no registers
   const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    for (int c = 64 * wv; c < pn[k]; c += 256)
+      if (c + lane < pn[k]) load_lds16(pb[k] + (uint32_t)(c + lane) * pitch, pd[k] + (uint32_t)c * 16u);
+  wait_lds_loads();
+  __syncthreads();
+  // results go through LDS and out in one coalesced store per block
+  __shared__ int32_t s_res[kSupportRunMax], s_ev[kSupportRunMax];
   const uint32_t bR = 0, bL = (uint32_t)(planes * nR) * 16u;
-  for (int k = k0 + wv; k < k1; k += 4) {
-    const int u = g.lu0 + k * g.step;
-    int result, ev = 0;
-    if (p.descriptor == 0) {
-      const LdsGrad cR{bR, (uint32_t)nR * 16u, cR0}, cL{bL, (uint32_t)nL * 16u, cL0};
-      const size_t ra = (size_t)(v - 2) * g.w * 16, rb = (size_t)(v + 2) * g.w * 16;
-      result = support_point_d(GradSelf{F.descL + ra, F.descL + rb},
-                               GradSelf{F.descR + ra, F.descR + rb}, cL, cR, u, g.w, p, lane,
-                               &ev);
+  if (p.descriptor == 0) {
+    const LdsGrad cR{bR, (uint32_t)nR * 16u, cR0}, cL{bL, (uint32_t)nL * 16u, cL0};
+    const size_t ra = (size_t)(v - 2) * g.w * 16, rb = (size_t)(v + 2) * g.w * 16;
+    support_runs(GradSelf{F.descL + ra, F.descL + rb}, GradSelf{F.descR + ra, F.descR + rb}, cL, cR,
+                 g, p, q, k0, k1, wv, lane, s_res, s_ev);
+  } else {
+    const size_t row = (size_t)l * g.w * p.cs_q * 16;
+    const uint8_t* const sL = reinterpret_cast<const uint8_t*>(F.csupL) + row;
+    const uint8_t* const sR = reinterpret_cast<const uint8_t*>(F.csupR) + row;
+    if (p.cs_q == 1) {
+      const LdsCensus<1> cR{bR, (uint32_t)nR * 16u, cR0}, cL{bL, (uint32_t)nL * 16u, cL0};
+      support_runs(CensusSelf<1>{sL}, CensusSelf<1>{sR}, cL, cR, g, p, q, k0, k1, wv, lane, s_res,
+                   s_ev);
     } else {
-      const size_t row = (size_t)l * g.w * p.cs_q;
-      if (p.cs_q == 1) {
-        const LdsCensus<1> cR{bR, (uint32_t)nR * 16u, cR0}, cL{bL, (uint32_t)nL * 16u, cL0};
-        result = support_point_d(CensusSelf<1>{F.csupL + row}, CensusSelf<1>{F.csupR + row}, cL,
-                                 cR, u, g.w, p, lane, &ev);
-      } else {
-        const LdsCensus<2> cR{bR, (uint32_t)nR * 16u, cR0}, cL{bL, (uint32_t)nL * 16u, cL0};
-        result = support_point_d(CensusSelf<2>{F.csupL + row}, CensusSelf<2>{F.csupR + row}, cL,
-                                 cR, u, g.w, p, lane, &ev);
-      }
-    }
-    if (lane == 0) {
-      s_res[k - k0] = result;
-      s_ev[k - k0] = ev;
+      const LdsCensus<2> cR{bR, (uint32_t)nR * 16u, cR0}, cL{bL, (uint32_t)nL * 16u, cL0};
+      support_runs(CensusSelf<2>{sL}, CensusSelf<2>{sR}, cL, cR, g, p, q, k0, k1, wv, lane, s_res,
+                   s_ev);
     }
   }
   __syncthreads();
