@@ -1129,7 +1129,10 @@ int batch_ctx(elas_handle* h, hipStream_t stream, BatchCtx** out) {
 // stores and loads; 16 pairs, 157 MB, even).
 constexpr uint64_t kDescNtBytes = 192ull << 20;
 
-// Frame tables and block prefixes of every launch, in one blob.
+// Frame tables and block prefixes of every launch, in one blob. A launch over
+// all frames takes the main table, and a stage without workgroups none: with a
+// table of its own for each tiled stage and prefixes for idle stages, a call
+// with 8 pairs of 640x480 took 212 us instead of 195 (1280x720: 442 and 423).
 void plan_batch(const std::vector<Frame>& frames, const std::vector<std::pair<int, int>>& var,
                 std::vector<LaunchRec>* recs, std::vector<uint8_t>* blob) {
   recs->clear();
@@ -1152,7 +1155,7 @@ void plan_batch(const std::vector<Frame>& frames, const std::vector<std::pair<in
                          : (st == kStageDense ? kDenseVariants
                                               : (st == kStageMatch ? kMatchVariants : 1));
     for (int v = 0; v < nvar; ++v) {
-      std::vector<Frame> sub;
+      std::vector<size_t> of;  // the frames of this launch
       std::vector<int32_t> starts(1, 0);
       size_t lds = 0;
       for (size_t i = 0; i < frames.size(); ++i) {
@@ -1162,21 +1165,26 @@ void plan_batch(const std::vector<Frame>& frames, const std::vector<std::pair<in
                                                 : match_variant(frames[i].g, frames[i].p));
         if (tiled && fv != v) continue;
         const int dv = tiled ? v : 0;
-        sub.push_back(frames[i]);
+        of.push_back(i);
         starts.push_back(starts.back() + stage_blocks(st, frames[i].g, frames[i].p, dv));
         lds = std::max(lds, stage_lds(st, frames[i].g, frames[i].p));
       }
-      if (sub.empty()) continue;
+      if (starts.back() == 0) continue;  // no workgroups, no launch
       LaunchRec r{};
       r.stage = st;
       r.variant = v;
-      r.nf = (int32_t)sub.size();
+      r.nf = (int32_t)of.size();
       r.total = starts.back();
       r.bpf = uniform_blocks(starts.data(), r.nf);
       r.desc_nt =
           (st == kStageDescriptor || st == kStageDense || st == kStageMatch) && desc_nt;
       r.lds = lds;
-      r.table_off = tiled ? put(sub.data(), sub.size() * sizeof(Frame)) : main_table;
+      r.table_off = main_table;
+      if (of.size() < frames.size()) {  // some frames only: a table of their own
+        std::vector<Frame> sub;
+        for (size_t i : of) sub.push_back(frames[i]);
+        r.table_off = put(sub.data(), sub.size() * sizeof(Frame));
+      }
       r.starts_off = put(starts.data(), starts.size() * sizeof(int32_t));
       recs->push_back(r);
     }
