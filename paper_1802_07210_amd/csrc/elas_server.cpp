@@ -80,6 +80,7 @@ struct elas_server {
   std::vector<hipEvent_t> free_events;  // ready events not in use
   elas_server_stats stats{};
   bool stop = false;
+  bool looking = false;  // a thread in elas_server_wait looks for its result
   std::string err;
   std::thread worker;
 };
@@ -149,9 +150,23 @@ bool release_idle(elas_server* S) {
   return any;
 }
 
+constexpr std::chrono::microseconds kLookAgain(300);
+
+// Without the lock for about two microseconds.
+void let_others(std::unique_lock<std::mutex>& lk) {
+  lk.unlock();
+  const auto until = Clock::now() + std::chrono::microseconds(2);
+  do
+    std::this_thread::yield();
+  while (Clock::now() < until);
+  lk.lock();
+}
+
 void worker_loop(elas_server* S) {
   std::unique_lock<std::mutex> lk(S->m);
+  Clock::time_point active = Clock::now();
   for (;;) {
+    bool launched = false;
     // completions
     bool any_done = false, any_busy = false;
     for (Slot& sl : S->slots) {
@@ -223,6 +238,7 @@ void worker_loop(elas_server* S) {
       sl.bytes = bytes;
       S->in_flight += bytes;
       S->stats.peak_bytes_in_flight = std::max(S->stats.peak_bytes_in_flight, S->in_flight);
+      launched = true;
       S->stats.batches += 1;
       S->stats.batched_pairs += (int64_t)pairs.size();
       lk.unlock();
@@ -262,10 +278,23 @@ void worker_loop(elas_server* S) {
       }
     }
     if (S->stop && S->queue.empty() && !any_busy) break;
-    if (!any_busy && S->queue.empty())
+    // Right after a completion or a launch the next event is usually near, and
+    // a timed wait returns tens of microseconds late (scheduler slack): look
+    // again at once for a while, then wait. One request of 640x480 is answered
+    // in 150 us instead of 203. With several batches in flight the device is
+    // the bound, and waiting lets requests gather.
+    const auto now = Clock::now();
+    if (any_done || launched) active = now;
+    int busy = 0;
+    for (const Slot& sl : S->slots) busy += sl.busy;
+    if (busy <= 1 && now - active < kLookAgain) {
+      let_others(lk);
+    } else if (!any_busy && S->queue.empty()) {
       S->work.wait(lk);
-    else
+      active = Clock::now();
+    } else {
       S->work.wait_for(lk, std::chrono::microseconds(20));
+    }
   }
 }
 
@@ -432,10 +461,19 @@ int elas_server_wait(elas_server* s, int64_t ticket, double* latency_ms) {
     return ELAS_ERR_ARG;
   }
   // submissions may rehash the table while this thread waits: look up again
-  s->done.wait(lk, [&] {
+  const auto over = [&] {
     auto i = s->results.find(ticket);
     return i == s->results.end() || i->second.state != State::Pending;
-  });
+  };
+  // one waiting thread looks for itself at first, as the worker does: being
+  // woken takes tens of microseconds
+  if (!s->looking) {
+    s->looking = true;
+    const auto until = Clock::now() + kLookAgain;
+    while (!over() && Clock::now() < until) let_others(lk);
+    s->looking = false;
+  }
+  s->done.wait(lk, over);
   it = s->results.find(ticket);
   if (it == s->results.end()) {
     s->err = "unknown ticket";
