@@ -550,6 +550,9 @@ def main():
     # share of chip time: duration x the fraction of the 256 CUs the kernel's
     # workgroups can occupy (launch geometry of each stage at this size)
     wgs = workgroups(W, H, D)
+    # the mesh spreads over lattice points, 36 per workgroup and view (384 in batches)
+    per, lattice = 36 if B == 1 else 384, ((W - 5) // 5) * ((H - 5) // 5)
+    wgs["mesh"] = 2 * (min(1024, max(1, -(-lattice // per))) + 1)
     chip_ms = {s: v * min(1.0, B * wgs[s] / 256.0) for s, v in kernel_ms.items()}
     dom = max(chip_ms, key=lambda k: chip_ms[k] if chip_ms[k] == chip_ms[k] else -1.0)
     wl = f"{W}x{H}_D{D}" + (f"_x{B}" if B > 1 else "")

@@ -4,8 +4,9 @@
 // Stage chain of elas_process on the caller's stream:
 //   k_descriptor (both views; Sobel or census) -> k_support -> k_filter
 //   [-> k_redun, past-only redundancy] -> k_rows -> mesh -> k_raster
-//   -> k_dense (both views) -> k_lrcheck [-> k_median].
-// The mesh step runs either on the device (k_mesh, the default: the frame
+//   -> k_match (matching of both views and their check; rows too wide for it:
+//   k_dense -> k_check) [-> k_median].
+// The mesh step runs either on the device (k_mesh, k_tris, the default: the frame
 // never returns to the host, so the call only enqueues work) or, with
 // mesh_on_host, on the host between the two GPU phases as in the paper's
 // CPU/FPGA split (Section IV, Fig. 3): wait for the per-row lists, gather
