@@ -705,18 +705,18 @@ int host_mesh_step(elas_handle* h, Buffers* b, hipStream_t stream) {
   const int32_t ntL = gotL, ntR = gotR;
   hd.ntri[0] = ntL;
   hd.ntri[1] = ntR;
-  if (ntL < capL) {  // the right view's records follow the left's
-    std::memmove(tris + ntL, tris + capL, (size_t)ntR * sizeof(RasterTri));
-    h->recsL.resize((size_t)ntL * 9);
-    h->planesL.resize((size_t)ntL * 3);
-  }
+  h->recsL.resize((size_t)ntL * 9);
+  h->planesL.resize((size_t)ntL * 3);
   h->recsR.resize((size_t)ntR * 9);
   h->planesR.resize((size_t)ntR * 3);
   uint8_t* hdr_host = static_cast<uint8_t*>(b->up_host) + tri_bytes;
   std::memcpy(hdr_host, &hd, sizeof(hd));
   h->hhdr = hd;
+  // the right view's records stay behind the left view's room (without corners
+  // the left view has fewer; what lies between is never read)
   if (ntL + ntR > 0)
-    HIP_TRY(hipMemcpyAsync(b->tris, b->up_host, (size_t)(ntL + ntR) * sizeof(RasterTri),
+    HIP_TRY(hipMemcpyAsync(b->tris, b->up_host,
+                           (size_t)(ntR > 0 ? capL + ntR : ntL) * sizeof(RasterTri),
                            hipMemcpyHostToDevice, stream));
   HIP_TRY(hipMemcpyAsync(b->hdr, hdr_host, sizeof(MeshHeader), hipMemcpyHostToDevice, stream));
   HIP_TRY(hipEventRecord(h->ev_upload, stream));

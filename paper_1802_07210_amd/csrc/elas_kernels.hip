@@ -1348,8 +1348,10 @@ __device__ __forceinline__ void raster_body(const Frame& F, int lb) {
   const int view = lb >= nb ? 1 : 0, band = lb - view * nb;
   const int v0 = band * band_rows, v1 = min(g.h - 1, v0 + band_rows - 1);
   const int rows = v1 - v0 + 1;
-  const int ntL = F.hdr->ntri[0], nt = view ? F.hdr->ntri[1] : ntL;
-  const RasterTri* vt = F.tris + (view ? ntL : 0);
+  // the right view's records start behind the room of the left view's 2n + 2,
+  // however many the left view has (none if its mesh failed)
+  const int nL = F.hdr->n[0], nt = F.hdr->ntri[view];
+  const RasterTri* vt = F.tris + (view && nL > 0 ? 2 * nL + 2 : 0);
   // the view's records as a wavefront-uniform base with 32-bit byte offsets
   // (24 B per record)
   const uint8_t* const vtb = reinterpret_cast<const uint8_t*>(vt);
