@@ -50,6 +50,7 @@
 // wavefront (the points along the border fall to few wavefronts: 43 us at
 // 640x480), one row per lane for listing and scanning (26 us).
 #include <algorithm>
+#include <type_traits>
 
 #include <hip/hip_ext.h>
 
@@ -154,6 +155,74 @@ __device__ __forceinline__ uint32_t point_key(const View<kStaged>& V, int i) {
   }
   const int e = V.rows[(size_t)lo * V.lw + (i - (int)mesh_smem[lo])];
   return make_key(e & 0xFFFF, V.lv0 + lo * V.step, (e >> 16) - V.dmin);
+}
+
+// The points of rows [r0, r1) whose columns may lie in [c0, c1], straight from
+// the row lists (views whose keys are not staged): sixteen lanes per row, four
+// rows per load, kRowLoads loads in flight. f(first row, i, key, in) gets the
+// lane's kRowLoads list positions and keys (with in false where a row has no
+// such point) and returns true to end the traversal; the result is the first
+// row of the step it ended in, or r1. A row is sorted by column: where rows are
+// long, its sixteen lanes first look at sixteen positions spread over it, and
+// it is read from the last of them left of the columns, until they are passed.
+// (By list position, each key found by a binary search among the row starts,
+// the mesh of 8 pairs of 640x480 with 7200 points a view took 1700 us instead of
+// 455, one such frame 447 instead of 125, one of 2560x1440 with 4200 points 326
+// instead of 158.)
+constexpr int kRowLoads = 2;
+template <class F>
+__device__ __forceinline__ int each_in_rows(const View<false>& V, int r0, int r1, int c0, int c1,
+                                            int lane, const F& f) {
+  const int sub = lane >> 4, pos = lane & 15;
+  const bool spread = V.n > 32 * V.lh;  // rows of more than 32 points on average
+  for (int rb = r0; rb < r1; rb += 4 * kRowLoads) {
+    int start[kRowLoads], cnt[kRowLoads], j[kRowLoads];
+    uint32_t row[kRowLoads], vkey[kRowLoads];  // the row's list and its keys' v part
+#pragma unroll
+    for (int k = 0; k < kRowLoads; ++k) {
+      const int l = min(rb + 4 * k + sub, V.lh - 1);
+      start[k] = (int)mesh_smem[l];
+      cnt[k] = (int)mesh_smem[l + 1] - start[k];
+      cnt[k] = rb + 4 * k + sub < r1 ? cnt[k] : 0;
+      row[k] = (uint32_t)l * (uint32_t)V.lw;
+      vkey[k] = make_key(0, V.lv0 + l * V.step, 0);
+      j[k] = pos;
+    }
+    if (spread) {
+      int e[kRowLoads];
+#pragma unroll
+      for (int k = 0; k < kRowLoads; ++k) e[k] = V.rows[row[k] + (uint32_t)((pos * cnt[k]) >> 4)];
+#pragma unroll
+      for (int k = 0; k < kRowLoads; ++k) {
+        const unsigned long long m = __builtin_amdgcn_ballot_w64((e[k] & 0xFFFF) < c0);
+        const uint32_t half = lane < 32 ? (uint32_t)m : (uint32_t)(m >> 32);
+        const int left = __popc((half >> (16 * (sub & 1))) & 0xFFFFu);  // positions left of c0
+        j[k] += left > 0 ? ((left - 1) * cnt[k]) >> 4 : 0;
+      }
+    }
+    for (;;) {
+      int i[kRowLoads], e[kRowLoads];
+      uint32_t key[kRowLoads];
+      bool in[kRowLoads];
+      int more = 0;
+#pragma unroll
+      for (int k = 0; k < kRowLoads; ++k) {
+        in[k] = j[k] < cnt[k];
+        i[k] = start[k] + j[k];
+        e[k] = V.rows[row[k] + (uint32_t)(in[k] ? j[k] : 0)];
+        j[k] += 16;
+      }
+#pragma unroll
+      for (int k = 0; k < kRowLoads; ++k) {
+        const int u = e[k] & 0xFFFF;
+        key[k] = ((uint32_t)u << 8) + (vkey[k] + (uint32_t)((e[k] >> 16) - V.dmin));
+        more |= (int)in[k] & (int)(u <= c1);
+      }
+      if (f(rb, i, key, in)) return rb;
+      if (!__builtin_amdgcn_ballot_w64(more != 0)) break;
+    }
+  }
+  return r1;
 }
 
 // ---- one search --------------------------------------------------------------
@@ -262,16 +331,17 @@ __device__ __forceinline__ Extent extent_of(const View<kStaged>& V, const Search
   return E;
 }
 
-// The points of list range [lo, hi) against *B. Most ranges hold none in the
+// The points of the extent's rows against *B. Most ranges hold none in the
 // circle, so they are first only tested for that, 64 kScan points at a time (N
 // against the bound times D, no division). From the first hit on every lane
 // keeps its best point and how close its second came; only if some lane's
 // second is within the error bound too (ties that fell into one lane) are the
 // points gone through once more.
 constexpr int kScan = 2;
-template <bool kStaged>
-__device__ __forceinline__ void scan_points(const View<kStaged>& V, const Search& S, int lo, int hi,
+__device__ __forceinline__ void scan_points(const View<true>& V, const Search& S, const Extent& E,
                                             int lane, Best* B) {
+  int lo = __builtin_amdgcn_readfirstlane((int)mesh_smem[E.r0]);
+  const int hi = __builtin_amdgcn_readfirstlane((int)mesh_smem[E.r1]);
   const float th = close_to((float)B->N * __builtin_amdgcn_rcpf((float)B->D));
   for (;; lo += 64 * kScan) {
     if (lo >= hi) return;
@@ -319,6 +389,67 @@ __device__ __forceinline__ void scan_points(const View<kStaged>& V, const Search
   }
 }
 
+// The same where the keys are not staged, over the extent's columns only.
+__device__ __forceinline__ void scan_points(const View<false>& V, const Search& S, const Extent& E,
+                                            int lane, Best* B) {
+  const float th = close_to((float)B->N * __builtin_amdgcn_rcpf((float)B->D));
+  const uint32_t best = B->key;
+  const int first = each_in_rows(
+      V, E.r0, E.r1, E.c0, E.c1, lane,
+      [&](int, const int(&)[kRowLoads], const uint32_t(&k)[kRowLoads], const bool(&in)[kRowLoads]) {
+        int hit = 0;
+#pragma unroll
+        for (int q = 0; q < kRowLoads; ++q) {
+          const int x = key_u(k[q]) - S.pu, y = key_v(k[q]) - S.pv;
+          const int D = __mul24(S.fx, y) - __mul24(S.fy, x);
+          const int N = __mul24(x, x - S.ex) + __mul24(y, y - S.ey);
+          hit |= (int)in[q] & (int)(D > 0) & (int)((float)N <= th * (float)D) & (int)(k[q] != best);
+        }
+        return __builtin_amdgcn_ballot_w64(hit != 0) != 0;
+      });
+  if (first >= E.r1) return;
+  float t1 = kNone, t2 = kNone;
+  uint32_t key = 0u;
+  int N = 0, D = 1;
+  auto eval = [&](uint32_t k, bool in, int* n, int* d) {
+    const int x = key_u(k) - S.pu, y = key_v(k) - S.pv;
+    const float t = evaluate(S, x, y, __mul24(x, x) + __mul24(y, y), n, d);
+    return in ? t : kNone;
+  };
+  each_in_rows(V, first, E.r1, E.c0, E.c1, lane,
+               [&](int, const int(&)[kRowLoads], const uint32_t(&k)[kRowLoads],
+                   const bool(&in)[kRowLoads]) {
+#pragma unroll
+                 for (int q = 0; q < kRowLoads; ++q) {
+                   int n, d;
+                   const float t = eval(k[q], in[q], &n, &d);
+                   t2 = fminf(t2, fmaxf(t1, t));
+                   const bool less = t < t1;
+                   key = less ? k[q] : key;
+                   N = less ? n : N;
+                   D = less ? d : D;
+                   t1 = less ? t : t1;
+                 }
+                 return false;
+               });
+  const float thr = close_to(fminf(wave_min_f32(t1), th));
+  if (!__builtin_amdgcn_ballot_w64(t2 <= thr)) {
+    offer(S, __builtin_amdgcn_ballot_w64(t1 <= thr), key, N, D, B);
+    return;
+  }
+  each_in_rows(V, first, E.r1, E.c0, E.c1, lane,
+               [&](int, const int(&)[kRowLoads], const uint32_t(&k)[kRowLoads],
+                   const bool(&in)[kRowLoads]) {
+#pragma unroll
+                 for (int q = 0; q < kRowLoads; ++q) {
+                   int n, d;
+                   const float t = eval(k[q], in[q], &n, &d);
+                   offer(S, __builtin_amdgcn_ballot_w64(t <= thr), k[q], n, d, B);
+                 }
+                 return false;
+               });
+}
+
 // The listed points: all points with u0 <= u < u1 in rows [l0, l1), and the
 // four corners; M of them, kListRegs per lane as keys and relative to p. reach:
 // a circle through p within this distance of it lies in the box.
@@ -362,8 +493,7 @@ __device__ __forceinline__ uint32_t search(const View<kStaged>& V, const Search&
   if ((C.R + fmaxf(fabsf(C.cx), fabsf(C.cy))) * 1.001f + 1.0f < L.reach) return B.key;
   const Extent E = extent_of(V, S, C);
   if (max(E.c0, 0) >= L.u0 && min(E.c1, w) < L.u1 && E.r0 >= L.l0 && E.r1 <= L.l1) return B.key;
-  scan_points(V, S, __builtin_amdgcn_readfirstlane((int)mesh_smem[E.r0]),
-              __builtin_amdgcn_readfirstlane((int)mesh_smem[E.r1]), lane, &B);
+  scan_points(V, S, E, lane, &B);
   return B.key;
 }
 
@@ -384,6 +514,7 @@ __host__ __device__ __forceinline__ int mesh_groups(const Geometry& g, bool batc
 // Single 640x480 13.3 us at 3, 14.7 at 3.5; 32 pairs 64 and 61 us.
 template <bool kBatch>
 constexpr float kHalo = kBatch ? 3.5f : 3.0f;
+constexpr float kHaloRows = 3.0f;  // keys not staged: seven rows of a lattice, not nine
 
 template <bool kBatch>
 __device__ __forceinline__ void mesh_body(const Frame& F, int lb) {
@@ -476,7 +607,8 @@ __device__ __forceinline__ void mesh_body(const Frame& F, int lb) {
     }
     __syncthreads();
   }
-  auto walks = [&](const auto& V) {
+  auto walks = [&](const auto& V, auto in_lds) {
+  constexpr bool kStaged = in_lds.value;
   const uint32_t corner[4] = {0u, make_key(g.w - 1, 0, 0), make_key(0, g.h - 1, 0),
                               make_key(g.w - 1, g.h - 1, 0)};
   List L;
@@ -496,12 +628,23 @@ __device__ __forceinline__ void mesh_body(const Frame& F, int lb) {
     for (int c = wid; c < 4; c += kWaves) {
       const int cu = key_u(corner[c]), cv = key_v(corner[c]);
       unsigned long long best = ~0ull;
-      for (int i = lane; i < n; i += 64) {
-        const uint32_t k = point_key(V, i);
+      auto near = [&](int i, uint32_t k) {
         const int du = key_u(k) - cu, dv = key_v(k) - cv;
         const unsigned long long x =
             ((unsigned long long)(uint32_t)(du * du + dv * dv) << 32) | (unsigned)i;
         best = x < best ? x : best;
+      };
+      if constexpr (kStaged) {
+        for (int i = lane; i < n; i += 64) near(i, point_key(V, i));
+      } else {
+        each_in_rows(V, 0, g.lh, 0, g.w, lane,
+                     [&](int, const int(&i)[kRowLoads], const uint32_t(&k)[kRowLoads],
+                         const bool(&in)[kRowLoads]) {
+#pragma unroll
+                       for (int q = 0; q < kRowLoads; ++q)
+                         if (in[q]) near(i[q], k[q]);
+                       return false;
+                     });
       }
       best = wave_min_u64(best);
       if (lane == 0)
@@ -525,7 +668,7 @@ __device__ __forceinline__ void mesh_body(const Frame& F, int lb) {
   int32_t* ptsR = F.ptsR;
   int32_t* pts = view ? ptsR : ptsL;
   const int max_rounds = min(F.p.mesh_max_rounds, kMeshMaxRounds);
-  const float half = kHalo<kBatch> * __builtin_amdgcn_sqrtf((float)g.w * (float)g.h / (float)n);
+  const float half = (kStaged ? kHalo<kBatch> : kHaloRows) * __builtin_amdgcn_sqrtf((float)g.w * (float)g.h / (float)n);
   const int hu0 = max(4, __builtin_amdgcn_readfirstlane((int)half));
   // a single frame's items are its wavefronts' (static); in a batch the
   // wavefronts of a workgroup take them as they finish
@@ -554,24 +697,35 @@ __device__ __forceinline__ void mesh_body(const Frame& F, int lb) {
       L.l1 = min(g.lh, pl + hl + 1);
       L.u0 = pu - hu;
       L.u1 = pu + hu + 1;
-      const int b0 = __builtin_amdgcn_readfirstlane((int)mesh_smem[L.l0]);
-      const int b1 = __builtin_amdgcn_readfirstlane((int)mesh_smem[L.l1]);
       M = 4;
-      constexpr int kList = 4;  // groups of 64 points at a time
-      for (int base = b0; base < b1; base += 64 * kList) {
-        uint32_t k[kList];
+      auto list = [&](uint32_t k, bool here) {
+        const int u = key_u(k);
+        const bool in = here && u >= L.u0 && u < L.u1;
+        const unsigned long long m = __builtin_amdgcn_ballot_w64(in);
+        const int pos = (int)__builtin_amdgcn_mbcnt_hi(
+            (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)M));
+        if (in && pos < kListCap) s_list[wid][pos] = k;
+        M += __popcll(m);
+      };
+      if constexpr (kStaged) {
+        const int b0 = __builtin_amdgcn_readfirstlane((int)mesh_smem[L.l0]);
+        const int b1 = __builtin_amdgcn_readfirstlane((int)mesh_smem[L.l1]);
+        constexpr int kList = 4;  // groups of 64 points at a time
+        for (int base = b0; base < b1; base += 64 * kList) {
+          uint32_t k[kList];
 #pragma unroll
-        for (int j = 0; j < kList; ++j) k[j] = point_key(V, min(base + 64 * j + lane, n - 1));
+          for (int j = 0; j < kList; ++j) k[j] = point_key(V, min(base + 64 * j + lane, n - 1));
 #pragma unroll
-        for (int j = 0; j < kList; ++j) {
-          const int u = key_u(k[j]);
-          const bool in = base + 64 * j + lane < b1 && u >= L.u0 && u < L.u1;
-          const unsigned long long m = __builtin_amdgcn_ballot_w64(in);
-          const int pos = (int)__builtin_amdgcn_mbcnt_hi(
-              (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)M));
-          if (in && pos < kListCap) s_list[wid][pos] = k[j];
-          M += __popcll(m);
+          for (int j = 0; j < kList; ++j) list(k[j], base + 64 * j + lane < b1);
         }
+      } else {
+        each_in_rows(V, L.l0, L.l1, L.u0, L.u1 - 1, lane,
+                     [&](int, const int(&)[kRowLoads], const uint32_t(&k)[kRowLoads],
+                         const bool(&in)[kRowLoads]) {
+#pragma unroll
+                       for (int q = 0; q < kRowLoads; ++q) list(k[q], in[q]);
+                       return M > kListCap && hu > 4;  // a smaller box is listed instead
+                     });
       }
       if (M > kListCap && hu > 4) {
         hu = max(4, hu * 3 / 4);
@@ -638,9 +792,9 @@ __device__ __forceinline__ void mesh_body(const Frame& F, int lb) {
   }
   };
   if (staged)
-    walks(View<true>{rows, n, g.lh, g.lw, g.lv0, g.step, dmin, koff});
+    walks(View<true>{rows, n, g.lh, g.lw, g.lv0, g.step, dmin, koff}, std::true_type{});
   else
-    walks(View<false>{rows, n, g.lh, g.lw, g.lv0, g.step, dmin, koff});
+    walks(View<false>{rows, n, g.lh, g.lw, g.lv0, g.step, dmin, koff}, std::false_type{});
 }
 
 // ---- k_tris -----------------------------------------------------------------
