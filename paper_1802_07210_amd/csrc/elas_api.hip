@@ -292,6 +292,7 @@ Geometry make_geometry(const elas_params& p, int32_t w, int32_t h) {
   // runs of 8 support points while runs of 16 would leave fewer than two
   // workgroups per CU, else 16 (less staging per point)
   g.srun = g.lh * ((g.lw + 15) / 16) < 512 ? 8 : 16;
+  g.mshare = kMeshShareFrame;
   g.gdiv = (uint32_t)(((1ull << 31) + (uint64_t)p.grid_size - 1) / (uint64_t)p.grid_size);
   g.rowmul = ((1ull << 40) + (uint64_t)w - 1) / (uint64_t)w;
   return g;
@@ -1344,6 +1345,9 @@ int elas::process_batch(elas_handle* h, int32_t n, const elas_pair* pairs, hipSt
     h->last_batch[i] = elas_handle::BatchPair{ph, b, stream, false};
     var.push_back(variants_lookup(h, q.w, q.h, ph->kp.D, true, ph->kp.descriptor != 0));
   }
+  int64_t lattice = 0;
+  for (const Frame& f : frames) lattice += (int64_t)f.g.lw * f.g.lh;
+  for (Frame& f : frames) f.g.mshare = mesh_share_batch(lattice);
   BatchCtx* c = nullptr;
   int rc = batch_ctx(h, stream, &c);
   if (rc != ELAS_OK) return rc;

@@ -30,6 +30,8 @@ struct Geometry {
   int32_t ftile;      // support-filter tile side in lattice points (8 or 16)
   int32_t srun;       // lattice points per support workgroup (8, 16 or 32; fewer
                       // when the staged columns would not fit in LDS)
+  int32_t mshare;     // lattice points per workgroup of the mesh's walks (a batched
+                      // call chooses it for its frames together)
   uint64_t rowmul;    // ceil(2^40 / w): row of pixel index px = (px * rowmul) >> 40,
                       // exact while px * w < 2^40 (px < 2^27, w <= 8192)
   uint32_t gdiv;      // ceil(2^31 / grid_size): x / grid_size = umulhi(2x, gdiv)
@@ -247,7 +249,11 @@ int32_t uniform_blocks(const int32_t* starts, int32_t nf);
 // The two mesh stages, kStageMesh and kStageTris (elas_mesh_device.hip), for
 // frames with both sides at most kDeviceMeshMaxSide: workgroups of one frame,
 // dynamic LDS of kStageMesh, and the launches.
-int32_t mesh_blocks(int32_t stage, const Geometry& g, bool batch);
+int32_t mesh_blocks(int32_t stage, const Geometry& g);
+// Geometry::mshare of a single frame, and of a batch whose frames have
+// `lattice` lattice points together.
+constexpr int32_t kMeshShareFrame = 36;
+int32_t mesh_share_batch(int64_t lattice);
 size_t mesh_lds(const Geometry& g);
 hipError_t launch_mesh_frame(int32_t stage, const Frame& f, hipStream_t s, hipEvent_t start,
                              hipEvent_t stop);

@@ -2427,7 +2427,7 @@ int32_t stage_blocks(int32_t stage, const Geometry& g, const KParams& p, int dv)
     case kStageRedun: return p.redundancy ? 1 : 0;
     case kStageRows: return g.lh;
     case kStageMesh:
-    case kStageTris: return mesh_blocks(stage, g, true);
+    case kStageTris: return mesh_blocks(stage, g);
     case kStageRaster: return 2 * cdiv(g.h, raster_band_rows(g.w));
     case kStageDense: return match_fused(g, p) ? 0 : dense_blocks(g, dv);
     case kStageCheck:

@@ -167,7 +167,7 @@ __device__ __forceinline__ uint32_t point_key(const View<kStaged>& V, int i) {
 // it is read from the last of them left of the columns, until they are passed.
 // (By list position, each key found by a binary search among the row starts,
 // the mesh of 8 pairs of 640x480 with 7200 points a view took 1700 us instead of
-// 455, one such frame 447 instead of 125, one of 2560x1440 with 4200 points 326
+// 340, one such frame 447 instead of 125, one of 2560x1440 with 4200 points 326
 // instead of 158.)
 constexpr int kRowLoads = 2;
 template <class F>
@@ -498,15 +498,15 @@ __device__ __forceinline__ uint32_t search(const View<kStaged>& V, const Search&
 }
 
 // ---- k_mesh ----------------------------------------------------------------
-// Workgroups per view, the last of which does the view's header, corner
-// disparities and top triangle. A single frame gets a wavefront per walk, two
-// per point (its latency is then one walk's); batches, which fill the chip
-// anyway, one per few points. The workgroup's points are spread over the view
+// Workgroups per view (one per Geometry::mshare lattice points), the last of
+// which does the view's header, corner disparities and top triangle. A single
+// frame gets a wavefront per walk, two per point (its latency is then one
+// walk's); batches one per point or few. The workgroup's points are spread over the view
 // and its wavefronts take them as they finish: a walk along the border takes
 // several times as long as one inside.
-__host__ __device__ __forceinline__ int mesh_groups(const Geometry& g, bool batch) {
-  const int nlat = g.lw * g.lh, per = batch ? 384 : 36;  // lattice points per workgroup
-  const int b = (nlat + per - 1) / per;
+__host__ __device__ __forceinline__ int mesh_groups(const Geometry& g) {
+  const int nlat = g.lw * g.lh;
+  const int b = (nlat + g.mshare - 1) / g.mshare;
   return (b < 1 ? 1 : (b > 1024 ? 1024 : b)) + 1;
 }
 // Half side of the listed box in point spacings sqrt(w h / n): a larger box
@@ -523,7 +523,7 @@ __device__ __forceinline__ void mesh_body(const Frame& F, int lb) {
   __shared__ uint32_t s_list[kWaves][kListCap];
   __shared__ int s_wsum[kWaves];
   const Geometry g = F.g;
-  const int groups = mesh_groups(g, kBatch);
+  const int groups = mesh_groups(g);
   const int view = lb >= groups ? 1 : 0, group = lb - view * groups;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1105,8 +1105,19 @@ size_t mesh_global_scratch_per_view(const Geometry& g) {
   return mesh_layout(nullptr, mesh_nmax(g), nullptr);
 }
 
-int32_t mesh_blocks(int32_t stage, const Geometry& g, bool batch) {
-  return 2 * (stage == kStageMesh ? mesh_groups(g, batch) : tris_groups(g));
+int32_t mesh_blocks(int32_t stage, const Geometry& g) {
+  return 2 * (stage == kStageMesh ? mesh_groups(g) : tris_groups(g));
+}
+
+// A workgroup has four wavefronts and stages its view's keys first, so shares of
+// a few points are the least and large ones the cheapest; between them the
+// workgroups of all frames together should be one resident round (1536 is six
+// per CU, seven fit): 8 pairs of 1280x720 59 us at 1536 workgroups, 67 at 3088,
+// 82 at 8128; 64 pairs of 128x128 26 us at 72 points each, 45 at 384. Above 384
+// points each the chip is full either way, and more rounds balance better (32
+// pairs of 640x480 75 us at 384, 87 at 768).
+int32_t mesh_share_batch(int64_t lattice) {
+  return (int32_t)std::min<int64_t>(384, std::max<int64_t>(72, 2 * lattice / 1500));
 }
 
 size_t mesh_lds(const Geometry& g) {
@@ -1116,7 +1127,7 @@ size_t mesh_lds(const Geometry& g) {
 hipError_t launch_mesh_frame(int32_t stage, const Frame& f, hipStream_t s, hipEvent_t start,
                              hipEvent_t stop) {
   if (f.g.w > kDeviceMeshMaxSide || f.g.h > kDeviceMeshMaxSide) return hipErrorInvalidValue;
-  const dim3 grid(mesh_blocks(stage, f.g, false)), block(kMeshT);
+  const dim3 grid(mesh_blocks(stage, f.g)), block(kMeshT);
   auto go = [&](auto kernel, uint32_t lds) {
     if (start || stop)
       hipExtLaunchKernelGGL(kernel, grid, block, lds, s, start, stop, 0u, f);

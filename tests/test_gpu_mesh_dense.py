@@ -75,7 +75,7 @@ def test_rows_instead_of_staged_keys(E, kind, batched):
 
 def test_a_point_costs_about_the_same_either_way(E):
     """8 pairs of 640x480 without redundancy: about 7200 points a view (lattice
-    step 5) against 3650 (step 7): 56 and 85 ns of one pair's view. Where every
+    step 5) against 3650 (step 7): 44 and 50 ns of one pair's view. Where every
     key was searched for among the row starts it was 201 and 84."""
     dev = torch.device("cuda:0")
     cfg = synth.SceneConfig(640, 480, 128, 24, 0.05, 4.0, 123.0, 2.0, 0.10, seed=3)
