@@ -250,9 +250,11 @@ enum elas_batch_flags {
                                    once and replay it */
   ELAS_BATCH_AUTOTUNE = 2       /* on the first batch with a new (w, h, D), time the
                                    descriptor (4/8/16 rows per block), dense (1/2/4
-                                   rows per block) and support (16/32 lattice points per
-                                   block) variants on its frames and keep the fastest;
-                                   results are identical for all */
+                                   rows per block; rows of more than 2112 columns,
+                                   census 3840, only: shorter ones are matched and
+                                   checked one by one) and support (16/32 lattice points
+                                   per block) variants on its frames and keep the
+                                   fastest; results are identical for all */
 };
 ELAS_API int elas_set_batch_flags(elas_handle* h, int32_t flags);
 
@@ -261,8 +263,8 @@ ELAS_API int elas_set_batch_flags(elas_handle* h, int32_t flags);
  * possibly different sizes and disparity ranges with one
  * launch per stage (and tile variant) for the whole batch: every stage's
  * kernel covers the workgroups of all frames, a workgroup finds its frame in
- * a device table (uploaded by the call from pinned memory), and the two mesh
- * workgroups of every frame run side by side. Equivalent, pair by pair, to
+ * a device table (uploaded by the call from pinned memory), and the mesh
+ * workgroups of all frames share the chip. Equivalent, pair by pair, to
  * elas_process with the pair's parameters; bit-identical outputs. Buffers
  * come from per-(size, stream) pools in the pair's parameter handle, so
  * batches on different streams run concurrently; a batch reuses them only
@@ -279,7 +281,9 @@ ELAS_API int elas_process_batch(elas_handle* h, int32_t n, const elas_pair* pair
 /* Tile variants the autotuner chose for (w, h) at this handle's disparity
  * count: descriptor rows per block, dense rows per block (the rows a
  * workgroup stages in LDS, the device's counterpart of the line buffers of
- * Section V-A) and support run length (lattice points per support workgroup,
+ * Section V-A; 2 where rows are short enough to be matched and checked one by
+ * one, up to 2112 columns or 3840 with census, which have no such tiles) and
+ * support run length (lattice points per support workgroup,
  * whose reachable descriptor columns it stages in LDS: 16 or 32 when tuned).
  * ELAS_ERR_ARG for null pointers or if none has been chosen yet. */
 ELAS_API int elas_get_tuned_variants(elas_handle* h, int32_t w, int32_t h_px,
@@ -288,7 +292,8 @@ ELAS_API int elas_get_tuned_variants(elas_handle* h, int32_t w, int32_t h_px,
 
 /* Fixes the tile variants of (w, h) at this handle's disparity count, as the
  * autotuner would (descriptor rows per block 4, 8 or 16; dense rows per
- * block 1, 2 or 4: the LDS row tiles of Section V-A's line buffers; support
+ * block 1, 2 or 4: the LDS row tiles of Section V-A's line buffers, of effect
+ * on rows of more than 2112 columns, census 3840, only; support
  * run length 8, 16 or 32 lattice points per workgroup); used by single and
  * batched calls, and the autotuner then leaves that size alone. Results do
  * not depend on the variants. ELAS_ERR_ARG for other values or a side below
