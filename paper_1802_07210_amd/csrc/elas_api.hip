@@ -1232,7 +1232,10 @@ int autotune(elas_handle* h, BatchCtx* c, const std::vector<Frame>& frames,
   const int32_t stages[3] = {kStageDescriptor, kStageDense, kStageSupport};
   std::vector<Frame> fr(frames);
   for (int k = 0; k < 3; ++k) {
-    if (k == 1 && match_fused(fr[0].g, fr[0].p)) continue;  // no dense tiles to choose
+    // no dense tiles to choose (frames of one size differ in this by descriptor)
+    if (k == 1 && std::all_of(fr.begin(), fr.end(),
+                              [](const Frame& f) { return match_fused(f.g, f.p); }))
+      continue;
     float best_ms = 1e30f;
     const int nvar = k == 0 ? kDescVariants : (k == 1 ? kDenseVariants : 2);
     for (int v = 0; v < nvar; ++v) {

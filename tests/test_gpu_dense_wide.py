@@ -82,3 +82,21 @@ def test_dense_tiles_of_a_batch_past_the_cache(E, rows):
         assert np.array_equal(items[i][2].cpu().numpy(), want[i % 3].outL)
         assert np.array_equal(items[i][3].cpu().numpy(), want[i % 3].outR)
     same(lambda name: e.batch_intermediate(n - 1, name), items[n - 1], want[(n - 1) % 3])
+
+
+def test_a_size_tuned_for_both_descriptors(E):
+    """At 2120 columns census rows are matched and checked in one kernel, gradient
+    rows are not: one call with both, tuned together."""
+    w, h, D = 2120, 40, 32
+    p = pair(w, h, D, 8)
+    census, plain = E.Elas(disp_max=D - 1, descriptor=1), E.Elas(disp_max=D - 1)
+    for order in ((census, plain), (plain, census)):
+        e = E.Elas(disp_max=D - 1)
+        items = [on_gpu(p) + (q,) for q in order]
+        for _ in range(2):
+            e.process_batch(items)
+        torch.cuda.synchronize()
+        assert e.tuned_variants(w, h)[1] in (1, 2, 4)
+        for i, q in enumerate(order):
+            t = ref.process(ref.params(disp_max=D - 1, descriptor=int(q is census)), p.left, p.right)
+            same(lambda name: e.batch_intermediate(i, name), items[i], t)
