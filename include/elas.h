@@ -22,8 +22,8 @@
  * ELAS_ERR_* code; no C++ exception crosses this interface. After a failure
  * elas_last_error() describes it. Work that fails on the device after a
  * call has returned (the device mesh reaching its walk limit or failing a
- * consistency check; its frame is then matched without plane priors, so its
- * maps differ from the reference pipeline) is reported as ELAS_ERR_INTERNAL:
+ * consistency check; its frame is then matched without plane priors, or with
+ * those of the faulty mesh, so its maps differ from the reference pipeline) is reported as ELAS_ERR_INTERNAL:
  * the failing kernel sets a pinned report word of the calling handle, and the
  * first later call on that handle (elas_process, elas_process_batch,
  * elas_process_noalloc, elas_get_stats) returns the error, once, without

@@ -76,12 +76,22 @@ struct MeshHeader {
   int32_t ntri[2];       // triangles (2n + 2, or 0 without support points)
   int32_t corners[8];    // d of the four image corners, left then right view
   int64_t support_evals; // support-search evaluations of the frame
-  int32_t status[2];     // 0; 1 if a walk hit its limit; 2 if the view's triangle
-                         // count failed its consistency check
+  int32_t status[2];     // 0; 1 if a walk hit its limit; 2 if the view's triangles
+                         // failed a consistency check (their count or cover)
   int32_t rounds[2];     // device mesh: most triangles owned by one point of each
                          // view (0 on the host)
   int32_t flips[2];      // 0 (the mesh is built without flips)
+  int32_t on_device[2];  // 1: the view was meshed on the device
 };
+
+// Whether triangles can cover a w x h image (its corner pixels' rectangle) once:
+// the sums, modulo 2^32, of a, a (u0 + u1 + u2) and a (v0 + v1 + v2) over them, a a
+// triangle's doubled area, are those of the rectangle's area and first moments. A
+// triangle missing, repeated in another's place or with a wrong vertex changes them.
+__host__ __device__ inline bool mesh_covers(const uint32_t (&sum)[3], int32_t w, int32_t h) {
+  const uint32_t x = (uint32_t)(w - 1), y = (uint32_t)(h - 1);
+  return sum[0] == 2u * x * y && sum[1] == 3u * x * x * y && sum[2] == 3u * x * y * y;
+}
 
 // ---- host mesh builder (elas_mesh.cpp) ----------------------------------
 // pts: n support points (u, v, d), all strictly inside the image; corners: d

@@ -1562,6 +1562,53 @@ __device__ __forceinline__ void raster_body(const Frame& F, int lb) {
   }
 }
 
+// Checks, once per frame and view, that the device mesh's raster records cover
+// the image (the host mesh checks itself); a view that does not is reported like
+// one whose walks failed. Workgroup-uniform; s_sum: three words of LDS. It runs
+// in workgroups that have little else to do: k_match's of the first and the last
+// row, or k_check's first two (in k_tris and the raster the sums cost 0.6 us of
+// every frame).
+__device__ __forceinline__ void check_cover(const Frame& F, const Geometry& g, int view,
+                                            uint32_t* s_sum) {
+  MeshHeader* const hdr = F.hdr;
+  const int nt = hdr->ntri[view], nL = hdr->n[0];
+  if (nt == 0 || hdr->on_device[view] == 0) return;
+  const int tid = threadIdx.x, lane = tid & 63, T = (int)blockDim.x;
+  const RasterTri* const tris = F.tris + (view ? 2 * nL + 2 : 0);
+  if (tid < 3) s_sum[tid] = 0u;
+  uint32_t sum[3] = {0u, 0u, 0u};
+  constexpr int kLoads = 4;
+  for (int t0 = 0; t0 < nt; t0 += kLoads * T) {
+    RasterTri R[kLoads];
+#pragma unroll
+    for (int k = 0; k < kLoads; ++k) R[k] = tris[min(t0 + k * T + tid, nt - 1)];
+#pragma unroll
+    for (int k = 0; k < kLoads; ++k) {
+      const int du1 = R[k].u[1] - R[k].u[0], dv1 = R[k].v[1] - R[k].v[0];
+      const int du2 = R[k].u[2] - R[k].u[0], dv2 = R[k].v[2] - R[k].v[0];
+      const uint32_t a = t0 + k * T + tid < nt ? (uint32_t)abs(du1 * dv2 - du2 * dv1) : 0u;
+      sum[0] += a;
+      sum[1] += a * (uint32_t)(R[k].u[0] + R[k].u[1] + R[k].u[2]);
+      sum[2] += a * (uint32_t)(R[k].v[0] + R[k].v[1] + R[k].v[2]);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const uint32_t x = (uint32_t)wave_sum_i32((int)sum[k]);
+    if (lane == 0) atomicAdd(&s_sum[k], x);
+  }
+  __syncthreads();
+  if (tid == 0) {
+    const uint32_t all[3] = {s_sum[0], s_sum[1], s_sum[2]};
+    if (!mesh_covers(all, g.w, g.h)) {
+      hdr->status[view] = 2;
+      int32_t* const mfail = F.mfail;
+      if (mfail) __hip_atomic_store(mfail, 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Dense matching (Section III-A, Fig. 1(h)). One thread per pixel; a block is
 // a 256-pixel row segment of R rows of one view (R = 1, 2 or 4: the tile
@@ -2046,6 +2093,8 @@ __device__ __forceinline__ void check_body(const Frame& F, int lb) {
     check_rows<true>(F, lb);
   else
     check_rows<false>(F, lb);
+  __shared__ uint32_t s_sum[3];
+  if (lb < 2) check_cover(F, F.g, lb, s_sum);
 }
 
 // ---------------------------------------------------------------------------
@@ -2208,6 +2257,7 @@ template <bool NT>
 __device__ __forceinline__ void match_rows(const Frame& F, int lb) {
   __shared__ int32_t s_lut[kLutSize];  // mirrored prior table, then zeros
   __shared__ int s_cnt[kMatchThreads / 64];
+  __shared__ uint32_t s_sum[3];
   const Geometry g = F.g;
   const KParams p = F.p;
   const int64_t begin = clock64();
@@ -2225,6 +2275,7 @@ __device__ __forceinline__ void match_rows(const Frame& F, int lb) {
     const float end = (float)(clock64() - begin);
     F.dense_counts[g.h + lb] = (int)(65536.f * (1.f - (float)(checking - begin) / end));
   }
+  if (lb == 0 || lb == g.h - 1) check_cover(F, g, lb == 0 ? 0 : 1, s_sum);
 }
 __device__ __forceinline__ void match_body(const Frame& F, int lb) { match_rows<false>(F, lb); }
 __device__ __forceinline__ void match_nt_body(const Frame& F, int lb) { match_rows<true>(F, lb); }

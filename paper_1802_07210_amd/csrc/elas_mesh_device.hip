@@ -574,6 +574,7 @@ __device__ __forceinline__ void mesh_body(const Frame& F, int lb) {
     hdr->ntri[view] = n > 0 ? 2 * n + 2 : 0;
     hdr->rounds[view] = 0;
     hdr->flips[view] = 0;
+    hdr->on_device[view] = 1;
     if (n == 0) {
       hdr->status[view] = 0;
       for (int c = 0; c < 4; ++c) hdr->corners[4 * view + c] = -1;
