@@ -675,6 +675,7 @@ __device__ __forceinline__ void support_group(const GS& gL, const GS& gR, const 
     s_ev[i] = textured ? n : 0;
   }
   const unsigned long long m = __builtin_amdgcn_ballot_w64(ok);
+  wave_sync();  // other lanes go on with these results
   uint32_t todo = 0;
 #pragma unroll
   for (int q = 0; q < F; ++q) todo |= (uint32_t)(m >> (kL * q) & 1) << q;

@@ -675,13 +675,14 @@ __device__ __forceinline__ void mesh_body(const Frame& F, int lb) {
   // wavefronts of a workgroup take them as they finish
   for (int item = group * kWaves + wid;; item += (groups - 1) * kWaves) {
     if constexpr (kBatch) {
-      // Lane 0 takes the next one; the others read it from LDS. The wave
-      // barriers are convergent, so the loop is not rotated around the
-      // lane-dependent branch: a register that only lane 0 sets would let
-      // the compiler send the other lanes round a loop of their own.
-      __builtin_amdgcn_wave_barrier();
+      // Lane 0 takes the next one; the others read it from LDS. wave_sync is
+      // convergent, so the loop is not rotated around the lane-dependent
+      // branch, and it orders memory, so no lane's read is replaced by its last
+      // one: a register that only lane 0 sets would let the compiler send the
+      // other lanes round a loop of their own.
+      wave_sync();
       if (lane == 0) s_take[wid] = atomicAdd(&s_next, 1);
-      __builtin_amdgcn_wave_barrier();
+      wave_sync();
       item = group + __builtin_amdgcn_readfirstlane(s_take[wid]) * (groups - 1);
     }
     if (item >= kWalks * n) break;
@@ -742,9 +743,9 @@ __device__ __forceinline__ void mesh_body(const Frame& F, int lb) {
     L.reach = fminf((float)hu, (float)((hl + 1) * g.step - 1));
     L.reach2 = (0.999f * L.reach - 1.0f) * (0.999f * L.reach - 1.0f);
     L.M = min(M, kListCap);
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     load_list(pu, pv);
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
 
     // the first neighbour, then the walks
     const uint32_t q0 = search(V, Search{p, pu, pv, 0, 0, 1, 0, 1}, L, g.w, lane);

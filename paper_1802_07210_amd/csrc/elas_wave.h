@@ -12,6 +12,15 @@
 
 namespace elas {
 
+// What lanes of the wavefront wrote to LDS before is seen by its other lanes
+// after. The barrier alone orders no memory for the compiler; neither it nor the
+// fences cost an instruction (a wavefront's LDS accesses are in order).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // DPP controls: quad permutes [1,0,3,2] and [2,3,0,1], row mirrors, row shifts
 constexpr int kDppQuadXor1 = 0xB1;
 constexpr int kDppQuadXor2 = 0x4E;
