@@ -66,8 +66,8 @@ PEAK_SAD_TOPS = 256 * 64 * 2.4e9 * 4 / 1e12    # 157.3 T byte-|diff| per second
 
 STAGES = ["descriptor", "support", "filter", "rows", "mesh", "raster", "dense", "lrcheck"]
 KERNEL_NAMES = {"descriptor": "k_descriptor8", "support": "k_support", "filter": "k_filter",
-                "rows": "k_rows", "mesh": "k_mesh", "raster": "k_raster", "dense": "k_match",
-                "lrcheck": "k_check"}  # (where rows are too wide for k_match, which checks as well)
+                "rows": "k_rows", "mesh": "k_mesh", "raster": "k_raster", "dense": "k_dense_r2",
+                "lrcheck": "k_check"}  # (rows up to 2112 columns: k_match in place of the last two)
 
 
 COPY_BYTES = 256 << 20
@@ -171,6 +171,8 @@ def algorithmic_work(stage: str, w: int, h: int, st: dict, pairs: int = 1):
         return 2 * 2 * 16 * w * max(1, st.get("lattice_rows", 0)) * pairs, 64 * st["support_evals"]
     if stage == "dense":        # own descriptor 16 B + prior 2 B read, raw 2 B written;
         return 2 * npx * (16 + 2 + 2), 16 * st["dense_evals"]       # 2 views
+    if stage == "match":        # both in one: own descriptor 16 B + prior 2 B read, raw and
+        return 2 * npx * (16 + 2 + 2 + 2), 16 * st["dense_evals"]   # checked 2 B written
     if stage == "lrcheck":      # read 2 B + partner 2 B, write 2 B per pixel, 2 views
         return 2 * npx * 6, 0
     if stage == "raster":       # a 4 B owner and a 2 B prior per pixel, 2 views
@@ -193,7 +195,29 @@ def workgroups(w: int, h: int, D: int, step: int = 5) -> dict:
             "filter": (cd(lw, 8) * cd(lh, 8) if cd(lw, 8) * cd(lh, 8) <= 256
                        else cd(lw, 16) * cd(lh, 16)), "rows": lh, "mesh": 2,
             "raster": 2 * cd(h, max(1, min(4, 4096 // w))),
-            "dense": 2 * cd(h, 2) * cd(w, 256), "lrcheck": 2 * cd(w * h, 1024)}
+            "dense": 2 * cd(h, 2) * cd(w, 256), "lrcheck": 2 * cd(w * h, 1024), "match": h}
+
+
+def mesh_workgroups(w: int, h: int, pairs: int, step: int = 5) -> int:
+    """Workgroups of the mesh's walks for one frame of a call with `pairs` of its
+    size: a share of the lattice each, and one more per view."""
+    lattice = ((w - 5) // step) * ((h - 5) // step)
+    share = 36 if pairs == 1 else min(384, max(72, 2 * lattice * pairs // 1500))
+    return 2 * (min(1024, max(1, -(-lattice // share))) + 1)
+
+
+def match_in_one(w: int) -> bool:
+    """Whether rows of w columns are matched and checked by one kernel."""
+    return 36 * (-(-w // 64) * 64) <= 76 * 1024
+
+
+def launched(stage_ms: dict, w: int) -> dict:
+    """Durations by launch: of the stage times, matching and check are the two
+    parts of one kernel where rows are short enough."""
+    out = {s: v for s, v in stage_ms.items() if s in KERNEL_NAMES}
+    if match_in_one(w):
+        out["match"] = out.pop("dense") + out.pop("lrcheck")
+    return out
 
 
 VALU_ISSUE_PEAK = 256 * 4 * 2.4e9 / 4   # wave64 VALU instructions per second (4 cycles each)
@@ -539,20 +563,17 @@ def main():
             host[k].append(tm[k])
     e.set_timing(False)
     stage_ms = {s: float(np.mean(v)) if v else float("nan") for s, v in acc.items()}
-    kernel_ms = {s: stage_ms[s] for s in KERNEL_NAMES}
-    names = dict(KERNEL_NAMES)
+    kernel_ms = launched(stage_ms, W)
+    names = {s: KERNEL_NAMES.get(s, "k_match") for s in kernel_ms}
     if B > 1:  # the batched kernels (their untuned tile variants; the raster's 256 threads;
         # descriptors by non-temporal stores and loads once a batch's reach 192 MiB)
         nt = "nt" if B * 32 * W * H >= (192 << 20) else ""
         names = {s: {"raster": "k_raster256", "descriptor": "k_descriptor16" + nt,
-                     "dense": "k_match" + nt}.get(s, n) + "_batch"
+                     "dense": "k_dense_r2" + nt, "match": "k_match" + nt}.get(s, n) + "_batch"
                  for s, n in names.items()}
     # share of chip time: duration x the fraction of the 256 CUs the kernel's
     # workgroups can occupy (launch geometry of each stage at this size)
-    wgs = workgroups(W, H, D)
-    # the mesh spreads over lattice points, 36 per workgroup and view (384 in batches)
-    per, lattice = 36 if B == 1 else 384, ((W - 5) // 5) * ((H - 5) // 5)
-    wgs["mesh"] = 2 * (min(1024, max(1, -(-lattice // per))) + 1)
+    wgs = dict(workgroups(W, H, D), mesh=mesh_workgroups(W, H, B))
     chip_ms = {s: v * min(1.0, B * wgs[s] / 256.0) for s, v in kernel_ms.items()}
     dom = max(chip_ms, key=lambda k: chip_ms[k] if chip_ms[k] == chip_ms[k] else -1.0)
     wl = f"{W}x{H}_D{D}" + (f"_x{B}" if B > 1 else "")
