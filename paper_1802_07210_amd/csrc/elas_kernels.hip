@@ -550,9 +550,10 @@ __device__ __forceinline__ Two two_rows(const Two& x, const Two& y) {
 // slots); of them the 16 SADs a candidate needs are under half. One point at a
 // time took 55.7 M instructions for 8 pairs of 1280x720 at 192 disparities and
 // 126 us; four at a time 51.8 M and 112 (8 pairs of 640x480: 38.5 and 35.3; one
-// frame of 1242x375: 16.8 and 14.5). Sharing the candidates' LDS reads among
-// the four (their columns overlap) was no gain: it costs scalar registers,
-// and the LDS reads are not the bound.
+// frame of 1242x375: 16.8 and 14.5). The LDS reads take about as long (16 bytes
+// per lane each: 77 us of 32 pairs of 640x480, beside 79 of vector issue), but
+// sharing them among the four, whose columns overlap, was no gain: it costs
+// scalar registers, which spill.
 // FULL: every lane of every step is in range for every point.
 template <int NJ, int G, int DIR, bool FULL, class GS, class C>
 __device__ __forceinline__ Two search(const GS& self, const C& other, const int (&u)[G],
@@ -2130,8 +2131,9 @@ constexpr size_t kMatchLds = 76 * 1024;
 // frame (its latency is the pieces of one wavefront) and for wide rows of a
 // batch, whose LDS admits few rows per CU; four for the rows of a batch of
 // which a CU holds six: a row's last round of pieces then wastes less (32
-// pairs of 640x480: 142 us with four, 165 with eight; 8 pairs of 1280x720: 142
-// and 110).
+// pairs of 640x480: 142 us with four, 165 with eight; 16 of 512x384 54 and 63; 8
+// of 704x528 and of 768x576 even; 8 of 832x624 79 and 71; 8 of 1280x720 142 and
+// 110).
 constexpr int kMatchThreads = 512;
 constexpr int kMatchBatchThreads[kMatchVariants] = {256, 512};
 

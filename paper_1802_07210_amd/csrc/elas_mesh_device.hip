@@ -43,12 +43,17 @@
 //
 // What bounds it: latency. A search is one dependent chain of ~0.4 us; a walk
 // is three to nine of them, and a point beside an empty part of the image adds
-// scans of ~0.8 us. k_mesh + k_tris, 640x480 13.3 + 6.4 us, 1280x720 21 + 8 us,
-// 32 pairs of 640x480 61 + 12 us (40 us of it is instruction issue); the
+// scans of ~0.8 us. k_mesh + k_tris, calls one at a time: 640x480 13 + 7 us,
+// 1280x720 23 + 11 (frame after frame on a stream 17 + 9 and 27 + 13); the
 // one-workgroup-per-view band triangulation with synchronous flip rounds that
-// this replaced took 58, 98 and 68 us. Measured and slower: a tile of points per
-// wavefront (the points along the border fall to few wavefronts: 43 us at
-// 640x480), one row per lane for listing and scanning (26 us).
+// this replaced took 58 and 98. Large batches fill the chip either way, and the
+// walks, whose arithmetic is the larger, gain nothing there: 32 pairs of 640x480
+// 64 + 12 us (before 68), of 1242x375 98 together (88), of 1280x720 140 + 21 (113);
+// about half of it is instruction issue. A walk is serial in its point's
+// neighbours: one point above a row of some hundred others takes 250 us.
+// Measured and slower: a tile of points per wavefront (the points along the
+// border fall to few wavefronts: 43 us at 640x480), one row per lane for listing
+// and scanning (26 us).
 #include <algorithm>
 #include <type_traits>
 
