@@ -2263,6 +2263,7 @@ __device__ __forceinline__ void match_rows(const Frame& F, int lb) {
   __shared__ uint32_t s_sum[3];
   const Geometry g = F.g;
   const KParams p = F.p;
+  if (lb == 0 || lb == g.h - 1) check_cover(F, g, lb == 0 ? 0 : 1, s_sum);
   const int64_t begin = clock64();
   int64_t checking;
   int cnt = p.descriptor ? match_row<CensusDense, NT>(F, g, p, lb, s_lut, &checking)
@@ -2278,7 +2279,6 @@ __device__ __forceinline__ void match_rows(const Frame& F, int lb) {
     const float end = (float)(clock64() - begin);
     F.dense_counts[g.h + lb] = (int)(65536.f * (1.f - (float)(checking - begin) / end));
   }
-  if (lb == 0 || lb == g.h - 1) check_cover(F, g, lb == 0 ? 0 : 1, s_sum);
 }
 __device__ __forceinline__ void match_body(const Frame& F, int lb) { match_rows<false>(F, lb); }
 __device__ __forceinline__ void match_nt_body(const Frame& F, int lb) { match_rows<true>(F, lb); }
